@@ -173,15 +173,54 @@ kmip::SelectShape choose_shape(int64_t N, int32_t H, int32_t d, int32_t k, int32
     return kmip::SelectShape{1, 8};
 }
 
-// Queries are grouped by direction (group.hip) and keys stored in bounded
-// superblocks (keyorder.hip) for a single graph large enough for the
-// pre-passes to pay off, at d <= 64 (the key-order kernels are built for
-// those widths).
-bool use_grouping(int64_t N, int32_t G, int32_t d) { return G == 1 && N >= 8192 && d <= 64; }
+// How a graph of n nodes is selected: scores in registers, two dense passes,
+// or the streaming kernel.
+enum SelectPath { kPathResident = 0, kPathDense = 1, kPathStream = 2 };
+// Dense passes cost n^2 d per head; for one graph the streaming kernel's
+// pre-passes cost about 0.5 ms and its time depends on how many key blocks
+// the bounds rule out.  For one graph the lines lie where the dense passes
+// are still faster on inputs that prune well (a point cloud, 4 heads, k = 32,
+// select with pre-passes, streaming against dense: 65k nodes at d = 16 1.87
+// against 1.18 ms, 46k at d = 32 1.54 against 0.95, 32k at d = 64 1.99 against
+// 0.83; 100k at d = 32 2.3 against more than 3); with many heads the
+// pre-passes weigh less (per head beyond the first, 45k nodes at d = 32: 157
+// against 224 us, 30k: 127 against 137).  At d = 128 and in a batch
+// nothing is pruned, but past 64k nodes the keys leave the L2 and the
+// streaming kernel, whose waves keep to the same tiles, is as fast.  Above
+// k = 128 the streaming kernel's trees leave room for one or two waves per
+// CU (k = 256, 200k nodes, 2 heads, d = 16: 27 against 14 ms).
+SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
+    if (n <= kmip::kResidentGraph && k <= KMIP_MAX_K_WIDE) return kPathResident;
+    int64_t most = 65536;
+    if (k > KMIP_MAX_K_WIDE)
+        most = 200000;
+    else if (G == 1 && d == 16)
+        most = H <= 8 ? 65536 : 49152;
+    else if (G == 1 && d == 32)
+        most = H <= 8 ? 46000 : 30000;
+    else if (G == 1 && d == 64)
+        most = 32768;
+    return n <= most ? kPathDense : kPathStream;
+}
 
-// The small-graph select keeps up to KMIP_MAX_K_WIDE candidates per query
-// in LDS and is built for d <= 64; other tasks go to the streaming kernel.
-bool small_select_ok(int32_t d, int32_t k) { return d <= 64 && k <= KMIP_MAX_K_WIDE; }
+// Queries are grouped by direction (group.hip) and keys stored in bounded
+// superblocks (keyorder.hip) for a single graph on the streaming path of at
+// least 8192 nodes, at d <= 64 (the key-order kernels are built for those
+// widths).
+// (The workspace holds the grouping and the order for every such graph,
+// whichever path takes it.)
+bool sized_for_grouping(int64_t N, int32_t G, int32_t d) { return G == 1 && N >= 8192 && d <= 64; }
+bool use_grouping(int64_t N, int32_t G, int32_t H, int32_t d, int32_t k) {
+    return sized_for_grouping(N, G, d) && select_path(N, G, H, d, k) == kPathStream;
+}
+
+// Queries per dense task: 64 share each key tile's load once the scan outweighs
+// the per-query work after it, where fewer workgroups would leave waves idle
+// (one head, d = 16: 20k nodes 65 us with 32, 77 with 64; 30k 112 and 104; one
+// head, d = 64: 9k nodes 58 and 64, 14k 86 and 82).  n: the largest graph.
+int32_t dense_run(int64_t n, int32_t d, int32_t k) {
+    return k <= 32 && (n + 31) / 32 * (d / 16 + 1) >= 1900 ? 64 : 32;
+}
 
 // Workspace of kmip_topk_prefilter, in order: the bf16 key tiles and the
 // select kernel's counters (for the query blocks it redoes), the int8 key
@@ -256,7 +295,7 @@ size_t kmip_topk_workspace_size(int64_t N, int32_t H, int32_t d, int32_t k, int3
     const int32_t G = num_graphs < 1 ? 1 : num_graphs;
     size_t bytes = tiled_bytes(N, H, d) + kCounterBytes;
     if (G > 1) bytes += align_up(max_tasks(N, G) * sizeof(kmip::Task));
-    if (use_grouping(N, G, d))
+    if (sized_for_grouping(N, G, d))
         bytes += align_up(kmip::group_workspace_bytes((int32_t)N, H, d)) +
                  align_up(kmip::key_order_workspace_bytes((int32_t)N, H, d));
     return bytes;
@@ -299,45 +338,54 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
     const kmip::SelectShape shape = choose_shape(N, H, d, k, G);
     const int32_t qb = shape.qb;
 
-    const kmip::Task* dtasks = nullptr;
-    int32_t ntasks = 0, nsmall = 0;
+    int64_t largest = N;
     if (G > 1) {
-        // Block-diagonal batch: one task per run of 32*qb queries of a graph,
-        // heaviest first (cost ~ queries x keys) to balance the tail.  The
-        // tasks of graphs of at most kSmallGraph nodes (runs of 32 queries)
-        // come first and go to the small-graph select (for the sizes it
-        // takes).
+        largest = 0;
+        for (int32_t g = 0; g < G; ++g) {
+            const int64_t n = graph_offsets[g + 1] - graph_offsets[g];
+            if (select_path(n, G, H, d, k) == kPathDense) largest = std::max(largest, n);
+        }
+    }
+    const int32_t run = dense_run(largest, d, k);
+    auto step_of = [&](int path) { return path == kPathResident ? 32 : path == kPathDense ? run : 32 * qb; };
+    // Tasks by path: [0, nres) resident, then ndense, then nstream.
+    const kmip::Task* dtasks = nullptr;
+    int32_t count[3] = {0, 0, 0};
+    if (G > 1) {
+        // Block-diagonal batch: one task per run of 32 queries (32*qb on the
+        // streaming path) of a graph, heaviest first within its path (cost ~
+        // queries x keys) to balance the tail.
         std::vector<kmip::Task> tasks;
         tasks.reserve(max_tasks(N, G));
-        for (int pass = 0; pass < 2; ++pass) {
+        for (int path = kPathResident; path <= kPathStream; ++path) {
             const size_t first = tasks.size();
             for (int32_t g = 0; g < G; ++g) {
                 const int32_t lo = graph_offsets[g], hi = graph_offsets[g + 1];
-                const bool small = hi - lo <= kmip::kSmallGraph && small_select_ok(d, k);
-                if (small != (pass == 0)) continue;
-                const int32_t step = small ? 32 : 32 * qb;
+                if (select_path(hi - lo, G, H, d, k) != path) continue;
+                const int32_t step = step_of(path);
                 for (int32_t q0 = lo; q0 < hi; q0 += step)
                     tasks.push_back(kmip::Task{q0, std::min(step, hi - q0), lo, hi});
             }
             std::stable_sort(tasks.begin() + first, tasks.end(), [](const kmip::Task& a, const kmip::Task& b) {
                 return (int64_t)a.q_count * (a.key_hi - a.key_lo) > (int64_t)b.q_count * (b.key_hi - b.key_lo);
             });
-            if (pass == 0) nsmall = (int32_t)tasks.size();
+            count[path] = (int32_t)(tasks.size() - first);
         }
-        ntasks = (int32_t)tasks.size() - nsmall;
         void* dst = ws + tiled_bytes(N, H, d) + kCounterBytes;
         hipError_t e = upload_async(dst, tasks.data(), tasks.size() * sizeof(kmip::Task), stream);
         if (e != hipSuccess) return hip_fail(e, "work list upload");
-        dtasks = reinterpret_cast<const kmip::Task*>(dst) + nsmall;
+        dtasks = reinterpret_cast<const kmip::Task*>(dst);
     } else {
-        ntasks = (int32_t)((N + 32 * qb - 1) / (32 * qb));
+        const SelectPath path = select_path(N, G, H, d, k);
+        const int32_t step = step_of(path);
+        count[path] = (int32_t)((N + step - 1) / step);
     }
 
     // A single large graph: queries grouped by direction, keys stored in
     // superblock order with bounds.
     kmip::QueryGroups groups{};
     kmip::KeyOrder keys{};
-    const bool grouped = use_grouping(N, G, d);
+    const bool grouped = use_grouping(N, G, H, d, k);
     if (grouped) {
         char* gws = ws + tiled_bytes(N, H, d) + kCounterBytes;
         hipError_t e = kmip::launch_group_queries(Q, n32, H, d, gws, &groups, stream);
@@ -346,23 +394,29 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
         e = kmip::launch_key_order(K, n32, H, d, ntiles, kws, &keys, stream);
         if (e != hipSuccess) return hip_fail(e, "key order launch");
     }
-    hipError_t e = kmip::launch_pack_k(K, grouped ? keys.perm : nullptr, grouped ? keys.rows : nullptr, kp, n32, H, d, ntiles,
-                                          stream);
-    if (e != hipSuccess) return hip_fail(e, "pack_k launch");
+    hipError_t e;
+    if (count[kPathDense] + count[kPathStream] > 0 &&
+        (e = kmip::launch_pack_k(K, grouped ? keys.perm : nullptr, grouped ? keys.rows : nullptr, kp, n32, H, d, ntiles,
+                                 stream)) != hipSuccess)
+        return hip_fail(e, "pack_k launch");
     int32_t* work_ctr = reinterpret_cast<int32_t*>(ws + tiled_bytes(N, H, d));
     hipEvent_t ev_start = reinterpret_cast<hipEvent_t>(select_start);
     hipEvent_t ev_stop = reinterpret_cast<hipEvent_t>(select_stop);
-    if (nsmall > 0) {
-        // the events bracket both select launches
-        if (ev_start != nullptr && (e = hipEventRecord(ev_start, stream)) != hipSuccess)
-            return hip_fail(e, "event record");
+    // the events bracket every select launch
+    if (count[kPathResident] + count[kPathDense] > 0 && ev_start != nullptr) {
+        if ((e = hipEventRecord(ev_start, stream)) != hipSuccess) return hip_fail(e, "event record");
         ev_start = nullptr;
-        e = kmip::launch_small_select(kp, Q, dtasks - nsmall, nsmall, n32, H, d, k, ntiles, topk_idx, stream);
-        if (e != hipSuccess) return hip_fail(e, "small-graph select launch");
     }
-    if (ntasks > 0) {
+    for (int path = kPathResident; path <= kPathDense; ++path) {
+        e = kmip::launch_dense_select(kp, K, Q, dtasks, count[path], n32, H, d, k, ntiles, step_of(path),
+                                      path == kPathResident,                                      topk_idx, stream);
+        if (e != hipSuccess) return hip_fail(e, "dense select launch");
+        if (dtasks != nullptr) dtasks += count[path];
+    }
+    if (count[kPathStream] > 0) {
         e = kmip::launch_select(kp, Q, K, dtasks, grouped ? &groups : nullptr, grouped ? &keys : nullptr,
-                                ntasks, n32, H, d, k, ntiles, shape, work_ctr, topk_idx, stream, ev_start, ev_stop);
+                                count[kPathStream], n32, H, d, k, ntiles, shape, work_ctr, topk_idx, stream, ev_start,
+                                ev_stop);
         if (e != hipSuccess) return hip_fail(e, "select launch");
     } else if (ev_stop != nullptr && (e = hipEventRecord(ev_stop, stream)) != hipSuccess) {
         return hip_fail(e, "event record");
@@ -464,7 +518,7 @@ kmip_status_t kmip_fwd_ex_with_events(const void* Q, const void* K, const void* 
     // that order too (the grouping is still in the workspace)
     const int32_t G = graph_offsets ? num_graphs : 1;
     const int32_t* perm = nullptr;
-    if (N > 0 && use_grouping(N, G, d))
+    if (N > 0 && use_grouping(N, G, H, d, k))
         perm = kmip::group_perm_in(reinterpret_cast<char*>(workspace) + tiled_bytes(N, H, d) + kCounterBytes,
                                    (int32_t)N, H, d);
     return attend_checked(Q, K, V, N, H, d, dv, k, scale, topk_idx, keep, drop_rate, perm, out, lse, stream);

@@ -1,0 +1,74 @@
+"""The dense select (scores in registers, or two passes over the keys) and the
+lines at which the library changes path, against the oracle.
+
+Integer inputs: the fp32 scores are exact and tie everywhere, so every row
+must equal the oracle's, order (score descending, index ascending) included.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from parity import check_structure, sample_rows
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2604_03815_amd as kmip  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).view(torch.bfloat16).to(DEV)
+
+
+EDGES = [1, 31, 32, 33, 0, 480, 511, 512, 513, 700]   # tiles, and the 512-key register path
+CASES = [
+    # (N, H, d, k, sizes, inputs)
+    *[(sum(EDGES), 2, d, k, EDGES, "ints") for d, k in ((16, 1), (32, 32), (64, 33), (128, 16), (128, 128), (32, 128))],
+    *[(2733, 1, 32, k, [600, 31, 2, 2100], "ints") for k in (129, 256, 257, 512)],
+    (512, 3, 32, 16, None, "ints"),
+    (513, 3, 32, 16, None, "ints"),
+    # lists that overflow: zero queries (every key ties), keys in order of score
+    *[(3000, 1, 32, k, s, kind) for k, s in ((10, None), (128, [500, 2500]), (300, None)) for kind in ("zeros", "sorted")],
+    # 64 queries a task; sampled first passes (every second, every third tile)
+    (31000, 1, 16, 32, None, "ints"),
+    (42000, 1, 16, 10, None, "ints"),
+    (16500, 1, 64, 4, None, "ints"),
+    (12000, 1, 64, 16, [400, 11600], "ints"),
+    # the last size of the dense path and the first of the streaming kernel
+    (46000, 1, 32, 16, None, "ints"),
+    (46001, 1, 32, 16, None, "ints"),
+    (65537, 1, 16, 10, None, "ints"),
+    (65700, 1, 16, 16, [100, 65600], "ints"),
+    (200001, 1, 16, 130, None, "ints"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "N%d_H%d_d%d_k%d_G%s_%s" % (*c[:4], c[4] and len(c[4]), c[5]))
+def test_rows_equal_oracle(case):
+    N, H, d, k, sizes, kind = case
+    rng = np.random.default_rng(N + d + k)
+    q = rng.integers(-2, 3, size=(N, H, d)).astype(np.float32)
+    kk = rng.integers(-1, 2, size=(N, H, d)).astype(np.float32)
+    if kind == "zeros":
+        q[rng.random(N) < 0.5] = 0
+    elif kind == "sorted":
+        q[:] = 1
+        kk[:] = 0
+        kk[:, :, 0] = np.minimum(np.arange(N) // 12, 255)[:, None]   # exact in bf16, twelve keys a score
+    offsets = None if sizes is None else np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    qb, kb = workloads.bf16_round(q), workloads.bf16_round(kk)
+    print(f"[case] dense select N={N} H={H} d={d} k={k} sizes={sizes} {kind}", flush=True)
+    idx = kmip.topk(_dev(qb), _dev(kb), k, graph_offsets=offsets)
+    torch.cuda.synchronize()
+    idx = idx.cpu().numpy()
+    check_structure(idx, offsets, N, H, k)
+    sel = None if N * H <= 8000 else sample_rows(N, H, 512, seed=5)
+    o_idx, _, _ = oracle.topk(oracle.from_bf16(qb), oracle.from_bf16(kb), k, offsets=offsets, **({} if sel is None else {"sel": sel}))
+    got = idx.reshape(N * H, k)
+    np.testing.assert_array_equal(got if sel is None else got[sel], o_idx)
