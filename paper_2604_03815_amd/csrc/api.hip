@@ -253,10 +253,11 @@ PrefilterLayout prefilter_layout(int64_t N, int32_t H, int32_t d) {
 }
 
 // kmip_attend_ex with an optional query order (perm [H][N], the forward's
-// grouping, or nullptr) for the order the aggregate takes query-heads in.
+// grouping, or nullptr) for the order the aggregate takes query-heads in, and
+// whether the call knows that the queries belong to one graph.
 kmip_status_t attend_checked(const void* Q, const void* K, const void* V, int64_t N, int32_t H, int32_t d,
                              int32_t dv, int32_t k, float scale, const int32_t* topk_idx, const uint8_t* keep,
-                             float drop_rate, const int32_t* perm, float* out, float* lse, void* stream_) {
+                             float drop_rate, const int32_t* perm, bool one_graph, float* out, float* lse, void* stream_) {
     kmip_status_t s = check_sizes(N, H, d, k);
     if (s != KMIP_OK) return s;
     if ((s = check_value_width(N, H, dv)) != KMIP_OK) return s;
@@ -268,7 +269,7 @@ kmip_status_t attend_checked(const void* Q, const void* K, const void* V, int64_
     if (!aligned16(Q) || !aligned16(K) || !aligned16(V))
         return record_error(KMIP_ERR_INVALID_ARG, "Q, K and V must be 16-byte aligned");
     hipError_t e = kmip::launch_attend(Q, K, V, topk_idx, keep, 1.0f / (1.0f - drop_rate), (int32_t)N, H, d, dv,
-                                       k, scale, perm, out, lse, reinterpret_cast<hipStream_t>(stream_));
+                                       k, scale, perm, one_graph, out, lse, reinterpret_cast<hipStream_t>(stream_));
     if (e != hipSuccess) return hip_fail(e, "attend launch");
     return ok();
 }
@@ -477,7 +478,8 @@ kmip_status_t kmip_topk_prefilter(const void* Q, const void* K, int64_t N, int32
 kmip_status_t kmip_attend_ex(const void* Q, const void* K, const void* V, int64_t N, int32_t H,
                              int32_t d, int32_t dv, int32_t k, float scale, const int32_t* topk_idx,
                              const uint8_t* keep, float drop_rate, float* out, float* lse, void* stream_) {
-    return attend_checked(Q, K, V, N, H, d, dv, k, scale, topk_idx, keep, drop_rate, nullptr, out, lse, stream_);
+    return attend_checked(Q, K, V, N, H, d, dv, k, scale, topk_idx, keep, drop_rate, nullptr, false, out, lse,
+                          stream_);
 }
 
 kmip_status_t kmip_attend(const void* Q, const void* K, const void* V, int64_t N, int32_t H,
@@ -521,7 +523,8 @@ kmip_status_t kmip_fwd_ex_with_events(const void* Q, const void* K, const void* 
     if (N > 0 && use_grouping(N, G, H, d, k))
         perm = kmip::group_perm_in(reinterpret_cast<char*>(workspace) + tiled_bytes(N, H, d) + kCounterBytes,
                                    (int32_t)N, H, d);
-    return attend_checked(Q, K, V, N, H, d, dv, k, scale, topk_idx, keep, drop_rate, perm, out, lse, stream);
+    return attend_checked(Q, K, V, N, H, d, dv, k, scale, topk_idx, keep, drop_rate, perm, G == 1, out, lse,
+                          stream);
 }
 
 kmip_status_t kmip_fwd(const void* Q, const void* K, const void* V, const int32_t* graph_offsets,

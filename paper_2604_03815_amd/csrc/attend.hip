@@ -6,167 +6,163 @@
 // scores are recomputed in fp32 from q_i and the gathered key rows, with the
 // same routine the backward uses, so the weights of the two passes agree.
 //
-// Mapping: a team of 16 lanes per (query, head), 16 teams per workgroup,
-// with the key slots on lanes (slot = lane + 16 s, NS slots per lane).  Each
-// lane gathers its slots' key rows (D = d_K wide) and forms their scores;
-// 16-lane butterflies give the softmax statistics; each lane then adds its
-// slots' weighted value rows (DV = d_V wide, gathered in the same round trip
-// as the key rows when they fit in 64 registers, else right after) into a
-// DV-vector, and a transposed team reduction leaves dimensions tl, tl + 16,
-// ... on lane tl.
+// Mapping: a team of 16 lanes per (query, head), 16 teams per workgroup (4 for
+// k > 128).  Rows are read by D/8 lanes each (gather.h), 128/D rows per team
+// and step.  The team's key indices go to LDS first; a step's lanes form
+// their rows' scores, which go to LDS beside the indices; the softmax runs
+// with the slots on lanes (slot = lane + 16 s); and the value rows are gathered
+// with the weights read back from LDS.  A team lies within a wave, whose LDS
+// instructions execute in order, so no barrier is needed.
+//
+// Bound by the cache lines the gathers look up (one a clock and CU), the round
+// trips and, where the rows of a head do not stay in L2, the fabric.  Against a
+// lane per row (us): 262k nodes, d = 64, k = 128 925 -> 340; 100k nodes, 4
+// heads, d = 32, k = 32 241 -> 162; 500k nodes, 4 heads, d = 16, k = 32 520 ->
+// 420; a batch of 128 graphs, d = 32, k = 16 37 -> 22.
 //
 // Attention dropout (keep != nullptr): slot t's weight in the sum is
 // multiplied by keep_scale when keep[qh k + t] is nonzero and by 0
 // otherwise; the softmax statistics (lse) are those before dropout.
 //
-// Order: with perm == nullptr, team t of block b takes query-head
-// 16 b + t.  With a query order perm [H][N] (the forward's grouping of the
-// queries by direction), block (b, h) takes positions 16 b .. 16 b + 15 of
-// head h in that order: queries of one group select mostly the same keys,
-// so the teams of a workgroup gather the same rows.
+// Order: without perm, the query-heads as they lie (neighbouring queries, all
+// heads), or one head after the other (head_blocks workgroups each, where
+// gather_by_head says so).  With a query order perm [H][N] (the forward's
+// grouping of the queries by direction), block (b, h) takes positions 16 b ..
+// 16 b + 15 of head h in that order: queries of one group select mostly the
+// same keys, so the teams of a workgroup gather the same rows.
+#include "gather.h"
 #include "kmip_device.h"
 #include "kmip_internal.h"
 
 namespace kmip {
 namespace {
 
-template <int D, int DV, int NS>
+// Words between the LDS areas of two teams: {index, score or weight} of every
+// slot (k rounded up to 16), and 16 words so that the four teams of a wave
+// meet different banks.
+__host__ __device__ constexpr int attend_stride(int k) { return 2 * ((k + 15) / 16 * 16) + 16; }
+
+template <int D, int DV>
 __global__ __launch_bounds__(256) void attend_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const int32_t* __restrict__ idx, const uint8_t* __restrict__ keep, float keep_scale, int32_t N,
-    int32_t H, int32_t k, float scale, const int32_t* __restrict__ perm, float* __restrict__ out,
+    int32_t H, int32_t k, float scale, const int32_t* __restrict__ perm, int32_t head_blocks, float* __restrict__ out,
     float* __restrict__ lse) {
-    constexpr bool kKeep = DV / 2 * NS <= 64;
-    const int tl = threadIdx.x & 15;
+    extern __shared__ int32_t lds[];
+    const int tl = threadIdx.x & 15, team = threadIdx.x >> 4, teams = blockDim.x >> 4;
     int64_t qh;
     int h;
-    if (perm != nullptr) {
-        h = blockIdx.y;
-        const int64_t p = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (perm != nullptr || head_blocks > 0) {
+        h = perm != nullptr ? blockIdx.y : blockIdx.x / head_blocks;
+        const int64_t p = (int64_t)(perm != nullptr ? blockIdx.x : blockIdx.x - h * head_blocks) * teams + team;
         if (p >= N) return;  // whole team exits together
-        qh = (int64_t)perm[(size_t)h * N + p] * H + h;
+        qh = (perm != nullptr ? (int64_t)perm[(size_t)h * N + p] : p) * H + h;
     } else {
-        qh = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+        qh = (int64_t)blockIdx.x * teams + team;
         if (qh >= (int64_t)N * H) return;  // whole team exits together
         h = (int)(qh % H);
     }
+    int2* const sh = reinterpret_cast<int2*>(lds + (size_t)team * attend_stride(k));
+    const int k16 = (k + 15) / 16 * 16;
+    for (int slot = tl; slot < k16; slot += 16) {
+        const int32_t j = slot < k ? idx[(size_t)qh * k + slot] : -1;
+        sh[slot].x = j >= 0 && j < N ? j : -1;
+    }
+    __builtin_amdgcn_wave_barrier();
 
-    float q[D];
-    load_row_f32<D>(q, Q + (size_t)qh * D);
-
-    float z[NS];
-    int32_t jj[NS];
-    uint4 vw[kKeep ? NS : 1][DV / 8];
-    float zmax = -INFINITY;
+    using KS = RowSplit<D>;
+    using VS = RowSplit<DV>;
+    {
+        float q[8];
+        widen8(q, *reinterpret_cast<const uint4*>(Q + (size_t)qh * D + 8 * (tl & (KS::LPR - 1))));
+        const int g = tl / KS::LPR;
+        const uint16_t* kcol = K + (size_t)h * D + 8 * (tl & (KS::LPR - 1));
+        for (int s0 = 0; s0 < k16; s0 += KS::RPT * KS::U) {
+            int32_t j[KS::U];
+            uint4 w[KS::U];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        z[s] = -INFINITY;
-        jj[s] = -1;
-        const int slot = tl + 16 * s;
-        if (slot < k) {
-            const int32_t j = idx[(size_t)qh * k + slot];
-            if (j >= 0 && j < N) {
-                jj[s] = j;
-                if constexpr (kKeep) load_row_words<DV>(vw[s], V + ((size_t)j * H + h) * DV);
-                z[s] = scale * dot_row_bf16<D>(q, K + ((size_t)j * H + h) * D);
+            for (int u = 0; u < KS::U; ++u) {
+                j[u] = sh[s0 + KS::RPT * u + g].x;
+                w[u] = *reinterpret_cast<const uint4*>(kcol + (size_t)(j[u] >= 0 ? j[u] : 0) * ((size_t)H * D));
+            }
+#pragma unroll
+            for (int u = 0; u < KS::U; ++u) {
+                const float z = scale * row_lanes_sum<KS::LPR>(dot8(q, w[u]));
+                if ((tl & (KS::LPR - 1)) == 0) sh[s0 + KS::RPT * u + g].y = __float_as_int(j[u] >= 0 ? z : -INFINITY);
             }
         }
-        zmax = fmaxf(zmax, z[s]);
     }
-    zmax = group16_max(zmax);
+    __builtin_amdgcn_wave_barrier();
 
-    float w[NS];
-    float zs = 0.0f;
+    // The first value rows go out before the softmax.
+    const int g = tl / VS::LPR;
+    const uint16_t* vcol = V + (size_t)h * DV + 8 * (tl & (VS::LPR - 1));
+    auto value_rows = [&](uint4 (&w)[VS::U], int s0) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        w[s] = jj[s] >= 0 ? __expf(z[s] - zmax) : 0.0f;
-        zs += w[s];
+        for (int u = 0; u < VS::U; ++u) {
+            const int32_t j = sh[s0 + VS::RPT * u + g].x;
+            w[u] = *reinterpret_cast<const uint4*>(vcol + (size_t)(j >= 0 ? j : 0) * ((size_t)H * DV));
+        }
+    };
+    uint4 w[VS::U];
+    value_rows(w, 0);
+
+    float zmax = -INFINITY;
+    for (int slot = tl; slot < k16; slot += 16) zmax = fmaxf(zmax, __int_as_float(sh[slot].y));
+    zmax = group16_max(zmax);
+    float zs = 0.0f;
+    for (int slot = tl; slot < k16; slot += 16) {
+        const int2 e = sh[slot];
+        float p = e.x >= 0 ? __expf(__int_as_float(e.y) - zmax) : 0.0f;
+        zs += p;
+        if (keep != nullptr && e.x >= 0) p *= keep[(size_t)qh * k + slot] != 0 ? keep_scale : 0.0f;
+        sh[slot].y = __float_as_int(p);
     }
     zs = group16_sum(zs);
-    if (keep != nullptr) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-            if (jj[s] >= 0) w[s] *= keep[(size_t)qh * k + tl + 16 * s] != 0 ? keep_scale : 0.0f;
-    }
+    __builtin_amdgcn_wave_barrier();
 
-    float acc[DV];
+    float acc[8];
 #pragma unroll
-    for (int t = 0; t < DV; ++t) acc[t] = 0.0f;
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (int s0 = 0;;) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        if (jj[s] >= 0) {
-            uint4 wv[DV / 8];
-            if constexpr (kKeep) {
-#pragma unroll
-                for (int c = 0; c < DV / 8; ++c) wv[c] = vw[s][c];
-            } else {
-                load_row_words<DV>(wv, V + ((size_t)jj[s] * H + h) * DV);
-            }
-#pragma unroll
-            for (int c = 0; c < DV / 8; ++c) {
-                const uint32_t ww[4] = {wv[c].x, wv[c].y, wv[c].z, wv[c].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[8 * c + 2 * e] = fmaf(w[s], bf16_bits_to_f32(ww[e] & 0xFFFFu), acc[8 * c + 2 * e]);
-                    acc[8 * c + 2 * e + 1] = fmaf(w[s], bf16_bits_to_f32(ww[e] >> 16), acc[8 * c + 2 * e + 1]);
-                }
-            }
+        for (int u = 0; u < VS::U; ++u) {
+            const int2 e = sh[s0 + VS::RPT * u + g];
+            if (e.x >= 0) axpy8(acc, __int_as_float(e.y), w[u]);
         }
+        s0 += VS::RPT * VS::U;
+        if (s0 >= k16) break;
+        value_rows(w, s0);
     }
-    float o[DV / 16];
-    team_sum_transpose<DV>(acc, o, tl);
-
+    scatter_rows_sum<DV>(acc, tl);
     const bool any = zmax != -INFINITY;
-    const float inv = any ? 1.0f / zs : 0.0f;
-#pragma unroll
-    for (int u = 0; u < DV / 16; ++u) out[(size_t)qh * DV + tl + 16 * u] = o[u] * inv;
+    store_scattered<DV>(out + (size_t)qh * DV, acc, any ? 1.0f / zs : 0.0f, tl);
     if (tl == 0) lse[qh] = any ? zmax + __logf(zs) : -INFINITY;
-}
-
-template <int D, int DV>
-void launch_attend_d(dim3 blocks, hipStream_t stream, const uint16_t* q, const uint16_t* kk,
-                     const uint16_t* v, const int32_t* idx, const uint8_t* keep, float keep_scale, int32_t N,
-                     int32_t H, int32_t k, float scale, const int32_t* perm, float* out, float* lse) {
-    const int ns = (k + 15) / 16;
-    if (ns <= 1)
-        hipLaunchKernelGGL((attend_kernel<D, DV, 1>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                           keep_scale, N, H, k, scale, perm, out, lse);
-    else if (ns <= 2)
-        hipLaunchKernelGGL((attend_kernel<D, DV, 2>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                           keep_scale, N, H, k, scale, perm, out, lse);
-    else if (ns <= 4)
-        hipLaunchKernelGGL((attend_kernel<D, DV, 4>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                           keep_scale, N, H, k, scale, perm, out, lse);
-    else if (ns <= 8)
-        hipLaunchKernelGGL((attend_kernel<D, DV, 8>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                           keep_scale, N, H, k, scale, perm, out, lse);
-    else if constexpr (D <= 64) {
-        // k > 128 (d <= 64 only)
-        if (ns <= 16)
-            hipLaunchKernelGGL((attend_kernel<D, DV, 16>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                               keep_scale, N, H, k, scale, perm, out, lse);
-        else
-            hipLaunchKernelGGL((attend_kernel<D, DV, 32>), dim3(blocks), dim3(256), 0, stream, q, kk, v, idx, keep,
-                               keep_scale, N, H, k, scale, perm, out, lse);
-    }
 }
 
 }  // namespace
 
 hipError_t launch_attend(const void* Q, const void* K, const void* V, const int32_t* idx,
                          const uint8_t* keep, float keep_scale, int32_t N, int32_t H, int32_t d, int32_t dv,
-                         int32_t k, float scale, const int32_t* perm, float* out, float* lse,
+                         int32_t k, float scale, const int32_t* perm, bool one_graph, float* out, float* lse,
                          hipStream_t stream) {
     const int64_t nqh = (int64_t)N * H;
     if (nqh == 0) return hipSuccess;
-    const dim3 blocks = perm != nullptr ? dim3((unsigned)((N + 15) / 16), (unsigned)H)
-                                        : dim3((unsigned)((nqh + 15) / 16));
+    // 16 teams a workgroup; with more than 128 slots a team's LDS area would
+    // leave few of them per CU, so a workgroup is one wave
+    const int teams = k > 128 ? 4 : 16;
+    const size_t lds = (size_t)teams * attend_stride(k) * sizeof(int32_t);
+    const int32_t per_head = (N + teams - 1) / teams, head_blocks = perm == nullptr && gather_by_head(N, H, d, dv, k, one_graph) ? per_head : 0;
+    const dim3 blocks = perm != nullptr   ? dim3((unsigned)per_head, (unsigned)H)
+                        : head_blocks > 0 ? dim3((unsigned)((int64_t)per_head * H))
+                                          : dim3((unsigned)((nqh + teams - 1) / teams));
     const uint16_t* q = reinterpret_cast<const uint16_t*>(Q);
     const uint16_t* kk = reinterpret_cast<const uint16_t*>(K);
     const uint16_t* v = reinterpret_cast<const uint16_t*>(V);
 #define KMIP_ATTEND_CASE(DD, DVV)                                                              \
     if (d == DD && dv == DVV) {                                                                \
-        launch_attend_d<DD, DVV>(blocks, stream, q, kk, v, idx, keep, keep_scale, N, H, k, scale, perm, out, lse); \
+        hipLaunchKernelGGL((attend_kernel<DD, DVV>), blocks, dim3(16 * teams), lds, stream, q, kk, v, idx, keep,  \
+                           keep_scale, N, H, k, scale, perm, head_blocks, out, lse);           \
         return hipGetLastError();                                                              \
     }
 #define KMIP_ATTEND_D(DD) \

@@ -20,6 +20,7 @@
 // Counting and placing aggregate equal key rows within a workgroup of 256
 // queries first, so a key that most queries select costs one global atomic
 // per workgroup, not one per pair.
+#include "gather.h"
 #include "kmip_device.h"
 #include "kmip_internal.h"
 
@@ -32,106 +33,202 @@ namespace {
 constexpr int kScanBlock = 1024;     // counts per block of the scan
 constexpr int kChunk = 1024;         // sorted pairs per wave in the reduction
 
-// 1. Per (query, head), a team of 16 lanes with the slots on lanes, NS
-// slots per lane (k <= 16 NS): p, dp, D, g of each selected pair, dQ_i, and
-// (QGt != nullptr, value width DV = D only) row qg_row of the interleaved
-// copy of q_i and dO_i.  D is the query/key width, DV the value width (dp_j runs
-// over it).  Slot tl + 16 s of query-head qh leaves its key index in jj[s]
-// (-1: none) and its coefficients a = scale g, p in ca[s], cp[s].  With
-// attention dropout (keep != nullptr, f = keep_scale or 0 by the slot's keep
-// draw) dp is replaced by f dp and the dV coefficient is p f.
+// 1. Per (query, head), a team of 16 lanes, NS slots per lane (k <= 16 NS):
+// p, dp, D, g of each selected pair, dQ_i, and (QGt != nullptr, value width
+// DV = D only) row qg_row of the interleaved copy of q_i and dO_i.  D is the
+// query/key width, DV the value width (dp_j runs over it).  Slot tl + 16 s
+// leaves its key index in jj[s] (-1: none) and its coefficients a = scale g, p
+// in ca[s], cp[s].  With attention dropout (keep != nullptr, f = keep_scale or
+// 0 by the slot's keep draw) dp is replaced by f dp and the dV coefficient is
+// p f.
+//
+// The inputs of a query-head (coef_fetch) are fetched apart, so that a team
+// that takes several fetches the next one's while it works on one.  Key and
+// value rows are read by D/8 and DV/8 lanes each (gather.h); a step's lanes
+// leave s and dp of their rows in the team's LDS area, from where each lane
+// takes its slots', and g goes back the same way for dQ.  Against a lane per
+// row the coefficient passes went from the cache's line lookups to the
+// round trips as their bound.
+template <int NS>
+struct CoefIn {
+    int32_t j[NS];   // this lane's key slots tl + 16 s (-1: none)
+    uint4 qw, gw;    // this lane's eight dimensions of q_i and dO_i
+    float l;         // lse (-inf: no key kept, or no query-head)
+    int64_t qh;
+    bool valid;
+};
+
 template <int D, int DV, int NS>
-__device__ __forceinline__ void coef_one(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                                         const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
-                                         const int32_t* __restrict__ idx, const float* __restrict__ lse,
-                                         const uint8_t* __restrict__ keep, float keep_scale,
-                                         int32_t N, int32_t H, int32_t k, float scale, int64_t qh, int tl,
-                                         float* __restrict__ dQ, uint16_t* __restrict__ QGt, size_t qg_row,
-                                         int32_t (&jj)[NS],
-                                         float (&ca)[NS], float (&cp)[NS]) {
-    // key rows kept in registers for dQ when they take at most 64 dwords a
-    // lane; otherwise read again (from cache)
-    constexpr bool kKeep = D / 2 * NS <= 64;
-    const int h = (int)(qh % H);
-    if (DV == D && QGt != nullptr && tl < D / 4) {
-        // interleaved copy: row qg_row holds q_i then dO_i, so the reduction
-        // gathers both with one load
-        const uint16_t* src = tl < D / 8 ? Q + (size_t)qh * D : dO + (size_t)qh * D;
-        reinterpret_cast<uint4*>(QGt + qg_row * (2 * D))[tl] = reinterpret_cast<const uint4*>(src)[tl & (D / 8 - 1)];
+__device__ __forceinline__ void coef_fetch(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ dO,
+                                           const int32_t* __restrict__ idx, const float* __restrict__ lse,
+                                           int32_t N, int32_t k, bool valid, int64_t qh, int tl, CoefIn<NS>& in) {
+    in.valid = valid;
+    in.qh = valid ? qh : 0;
+    in.l = -INFINITY;
+    in.qw = in.gw = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) in.j[s] = -1;
+    if (valid) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int slot = tl + 16 * s;
+            // a pair exists wherever its index lies in [0, N), as the counting
+            // pass sees it; its weight is zero if lse says no key was kept
+            const int32_t j = slot < k ? idx[(size_t)qh * k + slot] : -1;
+            in.j[s] = j >= 0 && j < N ? j : -1;
+        }
+        in.qw = *reinterpret_cast<const uint4*>(Q + (size_t)qh * D + 8 * (tl & (RowSplit<D>::LPR - 1)));
+        in.gw = *reinterpret_cast<const uint4*>(dO + (size_t)qh * DV + 8 * (tl & (RowSplit<DV>::LPR - 1)));
+        in.l = lse[qh];
     }
-    float q[D], g[DV];
-    load_row_f32<D>(q, Q + (size_t)qh * D);
-    load_row_f32<DV>(g, dO + (size_t)qh * DV);
-    const float l = lse[qh];
-    float p[NS], dp[NS], pv[NS];
-    uint4 kw[kKeep ? NS : 1][D / 8];
+}
+
+// Bytes of a team's LDS area: {s, dp} and the key index of every slot, and 16
+// words so that the four teams of a wave meet different banks.
+__host__ __device__ constexpr size_t coef_area(int ns) { return (size_t)ns * 16 * 12 + 64; }
+
+template <int D, int DV, int NS>
+__device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* __restrict__ K,
+                                          const uint16_t* __restrict__ V, const uint8_t* __restrict__ keep,
+                                          float keep_scale, int32_t H, int32_t k, float scale, int tl, char* area,
+                                          float* __restrict__ dQ, uint16_t* __restrict__ QGt, size_t qg_row,
+                                          int32_t (&jj)[NS], float (&ca)[NS], float (&cp)[NS]) {
+    using KS = RowSplit<D>;
+    using VS = RowSplit<DV>;
+    constexpr int K16 = 16 * NS;
+    constexpr int KST = K16 / KS::RPT;            // steps over the key rows
+    constexpr bool kKeep = 4 * KST <= 32;         // key rows kept in registers for dQ, else read again
+    float2* const sd = reinterpret_cast<float2*>(area);        // [K16] s, dp; then .x = g
+    int32_t* const js = reinterpret_cast<int32_t*>(sd + K16);  // [K16]
+    const int64_t qh = in.qh;
+    const int h = (int)(qh % H);
+    if constexpr (DV == D) {
+        // row qg_row of the interleaved copy, q_i then dO_i, so that the
+        // reduction gathers both with one load
+        if (QGt != nullptr && in.valid && tl < 2 * KS::LPR) {
+            const bool isq = tl < KS::LPR;   // (by component: a select of the two keeps them in memory)
+            reinterpret_cast<uint4*>(QGt + qg_row * (2 * D))[tl] =
+                make_uint4(isq ? in.qw.x : in.gw.x, isq ? in.qw.y : in.gw.y, isq ? in.qw.z : in.gw.z,
+                           isq ? in.qw.w : in.gw.w);
+        }
+    }
+    float q[8], g[8];
+    widen8(q, in.qw);
+    widen8(g, in.gw);
+    const bool live = in.l != -INFINITY;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        jj[s] = in.j[s];
+        js[tl + 16 * s] = live ? in.j[s] : -1;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int gk = tl / KS::LPR, gv = tl / VS::LPR;
+    const uint16_t* kcol = K + (size_t)h * D + 8 * (tl & (KS::LPR - 1));
+    const uint16_t* vcol = V + (size_t)h * DV + 8 * (tl & (VS::LPR - 1));
+    auto key_row = [&](int32_t j) {
+        return *reinterpret_cast<const uint4*>(kcol + (size_t)(j >= 0 ? j : 0) * ((size_t)H * D));
+    };
+    auto value_row = [&](int32_t j) {
+        return *reinterpret_cast<const uint4*>(vcol + (size_t)(j >= 0 ? j : 0) * ((size_t)H * DV));
+    };
+    uint4 kw[kKeep ? KST : 1];
+    auto dots = [&](int i0, auto keeps) {
+        // KS::U steps from i0 (equal widths: both rows; else the key rows)
+        int32_t j[KS::U];
+        uint4 a[KS::U], b[KS::U];
+#pragma unroll
+        for (int u = 0; u < KS::U; ++u) {
+            j[u] = js[KS::RPT * (i0 + u) + gk];
+            a[u] = key_row(j[u]);
+            if constexpr (DV == D) b[u] = value_row(j[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < KS::U; ++u) {
+            const float sv = row_lanes_sum<KS::LPR>(dot8(q, a[u]));
+            if constexpr (DV == D) {
+                const float dv = row_lanes_sum<KS::LPR>(dot8(g, b[u]));
+                if ((tl & (KS::LPR - 1)) == 0) sd[KS::RPT * (i0 + u) + gk] = make_float2(sv, dv);
+            } else {
+                if ((tl & (KS::LPR - 1)) == 0) sd[KS::RPT * (i0 + u) + gk].x = sv;
+            }
+            if constexpr (kKeep) keeps(u, a[u]);
+        }
+    };
+    if constexpr (kKeep) {
+#pragma unroll
+        for (int i0 = 0; i0 < KST; i0 += KS::U) dots(i0, [&](int u, const uint4& w) { kw[i0 + u] = w; });
+    } else {
+#pragma unroll 1
+        for (int i0 = 0; i0 < KST; i0 += KS::U) dots(i0, [](int, const uint4&) {});
+    }
+    if constexpr (DV != D) {
+#pragma unroll 1
+        for (int i0 = 0; i0 < K16 / VS::RPT; i0 += VS::U) {
+            uint4 b[VS::U];
+#pragma unroll
+            for (int u = 0; u < VS::U; ++u) b[u] = value_row(js[VS::RPT * (i0 + u) + gv]);
+#pragma unroll
+            for (int u = 0; u < VS::U; ++u) {
+                const float dv = row_lanes_sum<VS::LPR>(dot8(g, b[u]));
+                if ((tl & (VS::LPR - 1)) == 0) sd[VS::RPT * (i0 + u) + gv].y = dv;
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    // the slots on lanes
+    float p[NS], dp[NS];
     float dsum = 0.0f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        p[s] = 0.0f;
-        dp[s] = 0.0f;
-        pv[s] = 0.0f;
-        jj[s] = -1;
         const int slot = tl + 16 * s;
-        // a pair exists wherever its index lies in [0, N), as the counting
-        // pass sees it; its weight is zero if lse says no key was kept
-        const int32_t j = slot < k ? idx[(size_t)qh * k + slot] : -1;
-        if (j >= 0 && j < N) jj[s] = j;
-        if (j >= 0 && j < N && l != -INFINITY) {
-            {   // the key row (kept for dQ) and the two dot products
-                uint4 w[D / 8];
-                load_row_words<D>(w, K + ((size_t)j * H + h) * D);
-                if constexpr (kKeep) {
-#pragma unroll
-                    for (int c = 0; c < D / 8; ++c) kw[s][c] = w[c];
-                }
-                const float z = scale * dot_words_bf16<D>(q, w);
-                p[s] = __expf(z - l);
-                dp[s] = dot_row_bf16<DV>(g, V + ((size_t)j * H + h) * DV);
-                pv[s] = p[s];
-                if (keep != nullptr) {
-                    const float f = keep[(size_t)qh * k + slot] != 0 ? keep_scale : 0.0f;
-                    dp[s] *= f;
-                    pv[s] = p[s] * f;
-                }
+        p[s] = dp[s] = cp[s] = 0.0f;
+        if (jj[s] >= 0 && live) {
+            const float2 e = sd[slot];
+            p[s] = __expf(scale * e.x - in.l);
+            dp[s] = e.y;
+            cp[s] = p[s];
+            if (keep != nullptr) {
+                const float f = keep[(size_t)qh * k + slot] != 0 ? keep_scale : 0.0f;
+                dp[s] *= f;
+                cp[s] = p[s] * f;
             }
         }
         dsum = fmaf(p[s], dp[s], dsum);
     }
     dsum = group16_sum(dsum);
-    // dQ: each slot lane adds g_s k_j over its own slots, then the team
-    // reduces the D-vector so that lane tl ends up with dimensions tl, tl+16, ...
-    float acc[D];
-#pragma unroll
-    for (int t = 0; t < D; ++t) acc[t] = 0.0f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const float gs = p[s] * (dp[s] - dsum);
         ca[s] = scale * gs;
-        cp[s] = pv[s];
-        if (jj[s] >= 0 && l != -INFINITY) {
-            uint4 w[D / 8];
-            if constexpr (kKeep) {
+        sd[tl + 16 * s].x = gs;
+    }
+    __builtin_amdgcn_wave_barrier();
+    // dQ_i = scale sum_j g_j k_j
+    float acc[8];
 #pragma unroll
-                for (int c = 0; c < D / 8; ++c) w[c] = kw[s][c];
-            } else {
-                load_row_words<D>(w, K + ((size_t)jj[s] * H + h) * D);
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    if constexpr (kKeep) {
+#pragma unroll
+        for (int i = 0; i < KST; ++i)
+            if (js[KS::RPT * i + gk] >= 0) axpy8(acc, sd[KS::RPT * i + gk].x, kw[i]);
+    } else {
+#pragma unroll 1
+        for (int i0 = 0; i0 < KST; i0 += KS::U) {
+            int32_t j[KS::U];
+            uint4 w[KS::U];
+#pragma unroll
+            for (int u = 0; u < KS::U; ++u) {
+                j[u] = js[KS::RPT * (i0 + u) + gk];
+                w[u] = key_row(j[u]);
             }
 #pragma unroll
-            for (int c = 0; c < D / 8; ++c) {
-                const uint32_t ww[4] = {w[c].x, w[c].y, w[c].z, w[c].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[8 * c + 2 * e] = fmaf(gs, bf16_bits_to_f32(ww[e] & 0xFFFFu), acc[8 * c + 2 * e]);
-                    acc[8 * c + 2 * e + 1] = fmaf(gs, bf16_bits_to_f32(ww[e] >> 16), acc[8 * c + 2 * e + 1]);
-                }
-            }
+            for (int u = 0; u < KS::U; ++u)
+                if (j[u] >= 0) axpy8(acc, sd[KS::RPT * (i0 + u) + gk].x, w[u]);
         }
     }
-    float out[D / 16];
-    team_sum_transpose<D>(acc, out, tl);
-#pragma unroll
-    for (int u = 0; u < D / 16; ++u) dQ[(size_t)qh * D + 16 * u + tl] = scale * out[u];
+    __builtin_amdgcn_wave_barrier();   // the next query-head reuses the area
+    scatter_rows_sum<D>(acc, tl);
+    if (in.valid) store_scattered<D>(dQ + (size_t)qh * D, acc, scale, tl);
 }
 
 // The coefficients of every pair, in pair order (the segmented variant).
@@ -140,13 +237,23 @@ __global__ __launch_bounds__(256) void csr_coef_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const uint16_t* __restrict__ dO, const int32_t* __restrict__ idx, const float* __restrict__ lse,
     int32_t N, int32_t H, int32_t k, float scale, float* __restrict__ dQ, float2* __restrict__ coef,
-    uint16_t* __restrict__ QGt, const uint8_t* __restrict__ keep, float keep_scale) {
-    const int tl = threadIdx.x & 15;
-    const int64_t qh = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const uint8_t* __restrict__ keep, float keep_scale, int32_t head_blocks) {
+    extern __shared__ uint64_t lds[];
+    const int tl = threadIdx.x & 15, team = threadIdx.x >> 4;
+    int64_t qh = (int64_t)blockIdx.x * (blockDim.x >> 4) + team;
+    if (head_blocks > 0) {
+        const int h = blockIdx.x / head_blocks;
+        const int64_t i = (int64_t)(blockIdx.x - h * head_blocks) * (blockDim.x >> 4) + team;
+        if (i >= N) return;
+        qh = i * H + h;
+    }
     if (qh >= (int64_t)N * H) return;  // whole team exits together
+    CoefIn<NS> in;
+    coef_fetch<D, DV, NS>(Q, dO, idx, lse, N, k, true, qh, tl, in);
     int32_t jj[NS];
     float ca[NS], cp[NS];
-    coef_one<D, DV, NS>(Q, K, V, dO, idx, lse, keep, keep_scale, N, H, k, scale, qh, tl, dQ, QGt, 0, jj, ca, cp);
+    coef_team<D, DV, NS>(in, K, V, keep, keep_scale, H, k, scale, tl,
+                         reinterpret_cast<char*>(lds) + team * coef_area(NS), dQ, nullptr, 0, jj, ca, cp);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int slot = tl + 16 * s;
@@ -154,34 +261,33 @@ __global__ __launch_bounds__(256) void csr_coef_kernel(
     }
 }
 
-// Launches csr_coef_kernel<D, DV, NS> with NS the smallest power of two >= k/16.
+// Launches csr_coef_kernel<D, DV, NS> with NS the smallest power of two >=
+// k/16, 16 teams a workgroup (one wave for k > 128, whose LDS areas are large).
 template <int D, int DV>
-void launch_coef(unsigned blocks, hipStream_t stream, const uint16_t* q, const uint16_t* kk,
-                 const uint16_t* v, const uint16_t* g, const int32_t* idx, const float* lse, int32_t N,
-                 int32_t H, int32_t k, float scale, float* dQ, float2* coef, uint16_t* qg, const uint8_t* keep,
-                 float keep_scale) {
+void launch_coef(int64_t nh, hipStream_t stream, const uint16_t* q, const uint16_t* kk, const uint16_t* v,
+                 const uint16_t* g, const int32_t* idx, const float* lse, int32_t N, int32_t H, int32_t k,
+                 float scale, float* dQ, float2* coef, const uint8_t* keep, float keep_scale) {
     const int ns = (k + 15) / 16;
-    if (ns <= 1)
-        hipLaunchKernelGGL((csr_coef_kernel<D, DV, 1>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx, lse,
-                           N, H, k, scale, dQ, coef, qg, keep, keep_scale);
-    else if (ns <= 2)
-        hipLaunchKernelGGL((csr_coef_kernel<D, DV, 2>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx, lse,
-                           N, H, k, scale, dQ, coef, qg, keep, keep_scale);
-    else if (ns <= 4)
-        hipLaunchKernelGGL((csr_coef_kernel<D, DV, 4>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx, lse,
-                           N, H, k, scale, dQ, coef, qg, keep, keep_scale);
-    else if (ns <= 8)
-        hipLaunchKernelGGL((csr_coef_kernel<D, DV, 8>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx, lse,
-                           N, H, k, scale, dQ, coef, qg, keep, keep_scale);
-    else if constexpr (D <= 64) {
-        // k > 128 (d <= 64 only)
-        if (ns <= 16)
-            hipLaunchKernelGGL((csr_coef_kernel<D, DV, 16>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx,
-                               lse, N, H, k, scale, dQ, coef, qg, keep, keep_scale);
-        else
-            hipLaunchKernelGGL((csr_coef_kernel<D, DV, 32>), dim3(blocks), dim3(256), 0, stream, q, kk, v, g, idx,
-                               lse, N, H, k, scale, dQ, coef, qg, keep, keep_scale);
+#define KMIP_COEF(NSV)                                                                                          \
+    {                                                                                                           \
+        constexpr int teams = NSV > 8 ? 4 : 16;                                                                 \
+        const int32_t per_head = (N + teams - 1) / teams, head_blocks = gather_by_head(N, H, D, DV, k, false) ? per_head : 0; \
+        const int64_t blocks = head_blocks > 0 ? (int64_t)per_head * H : (nh + teams - 1) / teams;              \
+        hipLaunchKernelGGL((csr_coef_kernel<D, DV, NSV>), dim3((unsigned)blocks), dim3(16 * teams),             \
+                           teams * coef_area(NSV), stream, q, kk, v, g, idx, lse, N, H, k, scale, dQ, coef,     \
+                           keep, keep_scale, head_blocks);                                                      \
+        return;                                                                                                 \
     }
+    if (ns <= 1) KMIP_COEF(1)
+    if (ns <= 2) KMIP_COEF(2)
+    if (ns <= 4) KMIP_COEF(4)
+    if (ns <= 8) KMIP_COEF(8)
+    if constexpr (D <= 64) {
+        // k > 128 (d <= 64 only)
+        if (ns <= 16) KMIP_COEF(16)
+        KMIP_COEF(32)
+    }
+#undef KMIP_COEF
 }
 
 // Key row of slot s of query-head qh, or -1 (padding).
@@ -573,151 +679,6 @@ __device__ __forceinline__ int32_t wave_rank(int32_t* ctr, int32_t digit) {
     return base + (int32_t)__popcll(same & ((1ull << lane) - 1ull));
 }
 
-// Inputs of one query-head of the coefficient pass, fetched one query-head
-// ahead (coef_fetch) so that their loads overlap the previous query-head's
-// arithmetic (coef_compute).
-template <int D, int NS>
-struct CoefIn {
-    int32_t j[NS];       // this lane's key slots tl + 16 s (-1: none)
-    uint4 qw[D / 8];     // q_i and dO_i as bf16 words
-    uint4 gw[D / 8];
-    float l;             // lse (-inf: no key kept, or no query-head)
-    int64_t qh;
-    bool valid;          // u < N H
-};
-
-template <int D, int NS>
-__device__ __forceinline__ void coef_fetch(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ dO,
-                                           const int32_t* __restrict__ idx, const float* __restrict__ lse,
-                                           int32_t N, int32_t H, int32_t k, int64_t u, int64_t nh, int32_t i, int tl,
-                                           CoefIn<D, NS>& in) {
-    in.valid = u < nh;
-    const int32_t h = in.valid ? (int32_t)(u / N) : 0;
-    in.qh = (int64_t)i * H + h;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int slot = tl + 16 * s;
-        in.j[s] = in.valid && slot < k ? idx[(size_t)in.qh * k + slot] : -1;
-    }
-    if (in.valid) {
-        load_row_words<D>(in.qw, Q + (size_t)in.qh * D);
-        load_row_words<D>(in.gw, dO + (size_t)in.qh * D);
-        in.l = lse[in.qh];
-    } else {
-#pragma unroll
-        for (int c = 0; c < D / 8; ++c) in.qw[c] = in.gw[c] = make_uint4(0, 0, 0, 0);
-        in.l = -INFINITY;
-    }
-}
-
-// coef_one's arithmetic (value width D, with the interleaved copy) on
-// fetched inputs: the same operations in the same order, so the same bits.
-// (A coef_one built from coef_fetch and coef_compute, which would leave one
-// copy of the arithmetic, made the code the compiler emits for width 32
-// slower: the backward went from 1.10 to 1.39 ms on a 100k-node
-// graph at d = 32, so the two stay apart.)
-template <int D, int NS>
-__device__ __forceinline__ void coef_compute(const CoefIn<D, NS>& in, const uint16_t* __restrict__ K,
-                                             const uint16_t* __restrict__ V, const uint8_t* __restrict__ keep,
-                                             float keep_scale, int32_t N, int32_t H, int32_t k, float scale,
-                                             int tl, float* __restrict__ dQ, uint16_t* __restrict__ QGt,
-                                             size_t qg_row, int32_t (&jj)[NS], float (&ca)[NS], float (&cp)[NS]) {
-    constexpr bool kKeep = D / 2 * NS <= 64;
-    const int64_t qh = in.qh;
-    const int h = (int)(qh % H);
-    if (in.valid && tl < D / 4) {
-        // row qg_row of the interleaved copy: lane tl < D / 8 writes chunk tl
-        // of q_i, lane D / 8 + c chunk c of dO_i
-        uint4 v = in.qw[0];
-#pragma unroll
-        for (int c = 1; c < D / 8; ++c)
-            if (tl == c) v = in.qw[c];
-#pragma unroll
-        for (int c = 0; c < D / 8; ++c)
-            if (tl == D / 8 + c) v = in.gw[c];
-        reinterpret_cast<uint4*>(QGt + qg_row * (2 * D))[tl] = v;
-    }
-    float q[D], g[D];
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) {
-        const uint32_t wq[4] = {in.qw[c].x, in.qw[c].y, in.qw[c].z, in.qw[c].w};
-        const uint32_t wg[4] = {in.gw[c].x, in.gw[c].y, in.gw[c].z, in.gw[c].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            q[8 * c + 2 * e] = bf16_bits_to_f32(wq[e] & 0xFFFFu);
-            q[8 * c + 2 * e + 1] = bf16_bits_to_f32(wq[e] >> 16);
-            g[8 * c + 2 * e] = bf16_bits_to_f32(wg[e] & 0xFFFFu);
-            g[8 * c + 2 * e + 1] = bf16_bits_to_f32(wg[e] >> 16);
-        }
-    }
-    const float l = in.l;
-    float p[NS], dp[NS], pv[NS];
-    uint4 kw[kKeep ? NS : 1][D / 8];
-    float dsum = 0.0f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        p[s] = 0.0f;
-        dp[s] = 0.0f;
-        pv[s] = 0.0f;
-        jj[s] = -1;
-        const int slot = tl + 16 * s;
-        const int32_t j = in.j[s];
-        if (j >= 0 && j < N) jj[s] = j;
-        if (j >= 0 && j < N && l != -INFINITY) {
-            uint4 w[D / 8];
-            load_row_words<D>(w, K + ((size_t)j * H + h) * D);
-            if constexpr (kKeep) {
-#pragma unroll
-                for (int c = 0; c < D / 8; ++c) kw[s][c] = w[c];
-            }
-            const float z = scale * dot_words_bf16<D>(q, w);
-            p[s] = __expf(z - l);
-            dp[s] = dot_row_bf16<D>(g, V + ((size_t)j * H + h) * D);
-            pv[s] = p[s];
-            if (keep != nullptr) {
-                const float f = keep[(size_t)qh * k + slot] != 0 ? keep_scale : 0.0f;
-                dp[s] *= f;
-                pv[s] = p[s] * f;
-            }
-        }
-        dsum = fmaf(p[s], dp[s], dsum);
-    }
-    dsum = group16_sum(dsum);
-    float acc[D];
-#pragma unroll
-    for (int t = 0; t < D; ++t) acc[t] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const float gs = p[s] * (dp[s] - dsum);
-        ca[s] = scale * gs;
-        cp[s] = pv[s];
-        if (jj[s] >= 0 && l != -INFINITY) {
-            uint4 w[D / 8];
-            if constexpr (kKeep) {
-#pragma unroll
-                for (int c = 0; c < D / 8; ++c) w[c] = kw[s][c];
-            } else {
-                load_row_words<D>(w, K + ((size_t)jj[s] * H + h) * D);
-            }
-#pragma unroll
-            for (int c = 0; c < D / 8; ++c) {
-                const uint32_t ww[4] = {w[c].x, w[c].y, w[c].z, w[c].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[8 * c + 2 * e] = fmaf(gs, bf16_bits_to_f32(ww[e] & 0xFFFFu), acc[8 * c + 2 * e]);
-                    acc[8 * c + 2 * e + 1] = fmaf(gs, bf16_bits_to_f32(ww[e] >> 16), acc[8 * c + 2 * e + 1]);
-                }
-            }
-        }
-    }
-    float out[D / 16];
-    team_sum_transpose<D>(acc, out, tl);
-    if (in.valid) {
-#pragma unroll
-        for (int u = 0; u < D / 16; ++u) dQ[(size_t)qh * D + 16 * u + tl] = scale * out[u];
-    }
-}
-
 // The coefficient pass fused with placement pass 1: a
 // workgroup takes 128 / NS query-heads (8 / NS per team, at most 2048
 // pairs), computes their coefficients, dQ and the interleaved copy, and
@@ -743,48 +704,39 @@ __global__ __launch_bounds__(256) void coef_split_kernel(
     constexpr int R = TQ * NS;   // records per lane: 8
     static_assert(256 * R == kSplitChunk, "one staging chunk per workgroup");
     __shared__ int32_t cnt[kMaxSup], lstart[kMaxSup], gbase[kMaxSup];
-    __shared__ PairRecord stage[kSplitChunk];
+    __shared__ PairRecord stage[kSplitChunk];   // the teams' areas before
+    static_assert(16 * coef_area(NS) <= sizeof(stage), "the areas fit the staging chunk");
     __shared__ int32_t total;
     const int t = threadIdx.x;
     const int tl = t & 15, team = t >> 4;
     const int64_t nh = (int64_t)N * H;
     if (t < kMaxSup) cnt[t] = 0;
+    char* const area = reinterpret_cast<char*>(stage) + team * coef_area(NS);
     PairRecord rr[R];
     int32_t sup[R], slot[R];
-    // With narrow rows the inputs of a team's next query-head are fetched
-    // while the current one computes (the query rows of all of them first);
-    // wider rows would not leave the registers for it.
-    constexpr bool kAhead = D == 16 || (D == 32 && NS == 1);
+    // the query rows of a team first, then each query-head's inputs while the
+    // one before computes
+    const int64_t u0 = (int64_t)blockIdx.x * (16 * TQ) + team;
     int32_t qrow[TQ];
-    CoefIn<D, NS> nxt;
-    if constexpr (kAhead) {
-#pragma unroll
-        for (int it = 0; it < TQ; ++it) {
-            const int64_t u = (int64_t)blockIdx.x * (16 * TQ) + it * 16 + team;
-            qrow[it] = u < nh ? perm[u] : 0;
-        }
-        coef_fetch<D, NS>(Q, dO, idx, lse, N, H, k, (int64_t)blockIdx.x * (16 * TQ) + team, nh, qrow[0], tl, nxt);
-    }
 #pragma unroll
     for (int it = 0; it < TQ; ++it) {
-        const int64_t u = (int64_t)blockIdx.x * (16 * TQ) + it * 16 + team;
+        const int64_t u = u0 + it * 16;
+        qrow[it] = u < nh ? perm[u] : 0;
+    }
+    CoefIn<NS> nxt;
+    coef_fetch<D, D, NS>(Q, dO, idx, lse, N, k, u0 < nh, (int64_t)qrow[0] * H + (u0 < nh ? u0 / N : 0), tl, nxt);
+#pragma unroll
+    for (int it = 0; it < TQ; ++it) {
+        const int64_t u = u0 + it * 16;
         const int32_t h = u < nh ? (int32_t)(u / N) : 0;
         int32_t jj[NS];
         float ca[NS], cp[NS];
-        if constexpr (kAhead) {
-            const CoefIn<D, NS> cur = nxt;
-            if (it + 1 < TQ)
-                coef_fetch<D, NS>(Q, dO, idx, lse, N, H, k, u + 16, nh, qrow[it + 1], tl, nxt);
-            coef_compute<D, NS>(cur, K, V, keep, keep_scale, N, H, k, scale, tl, dQ, QGt, (size_t)u, jj, ca, cp);
-        } else {
-            const int32_t i = u < nh ? perm[u] : 0;
-            const int64_t qh = (int64_t)i * H + h;
-#pragma unroll
-            for (int s2 = 0; s2 < NS; ++s2) jj[s2] = -1;
-            if (u < nh)
-                coef_one<D, D, NS>(Q, K, V, dO, idx, lse, keep, keep_scale, N, H, k, scale, qh, tl, dQ, QGt,
-                                   (size_t)u, jj, ca, cp);
+        const CoefIn<NS> cur = nxt;
+        if (it + 1 < TQ) {
+            const int64_t v = u + 16;
+            coef_fetch<D, D, NS>(Q, dO, idx, lse, N, k, v < nh, (int64_t)qrow[it + 1] * H + (v < nh ? v / N : 0), tl, nxt);
         }
+        coef_team<D, D, NS>(cur, K, V, keep, keep_scale, H, k, scale, tl, area, dQ, QGt, (size_t)u, jj, ca, cp);
 #pragma unroll
         for (int s2 = 0; s2 < NS; ++s2) {
             const int r = it * NS + s2;
@@ -1318,12 +1270,10 @@ hipError_t launch_bwd_csr(const void* Q, const void* K, const void* V, const voi
     if ((e = launch_fill_zero(reinterpret_cast<float*>(cnt), ((size_t)nh + 3) / 4 * 4, stream)) != hipSuccess) return e;
     if ((e = launch_fill_zero(dK, (size_t)nh * d, stream)) != hipSuccess) return e;
     if ((e = launch_fill_zero(dV, (size_t)nh * dv, stream)) != hipSuccess) return e;
-    const unsigned team_blocks = (unsigned)((nh + 15) / 16);
     bool launched = false;
 #define KMIP_CSR_COEF(DD, DVV)                                                                          \
     if (d == DD && dv == DVV) {                                                                         \
-        launch_coef<DD, DVV>(team_blocks, stream, q, kk, v, g, idx, lse, N, H, k, scale, dQ, coef, nullptr, \
-                             keep, keep_scale);                                                          \
+        launch_coef<DD, DVV>(nh, stream, q, kk, v, g, idx, lse, N, H, k, scale, dQ, coef, keep, keep_scale); \
         launched = true;                                                                                \
     }
 #define KMIP_CSR_COEF_D(DD) KMIP_CSR_COEF(DD, 16) KMIP_CSR_COEF(DD, 32) KMIP_CSR_COEF(DD, 64) KMIP_CSR_COEF(DD, 128)

@@ -48,9 +48,9 @@ __device__ __forceinline__ void load_row_words(uint4 (&w)[D / 8], const uint16_t
 }
 
 // Dot product of a float32 query row held in registers with a bf16 row,
-// accumulated in float32 in dimension order t = 0..D-1.  The aggregate and
-// the backward kernels both go through this one function, so they see
-// bit-identical scores.
+// accumulated in float32 in dimension order t = 0..D-1 (the per-pair and
+// key-aggregated backward; the aggregate and the sorted backward share
+// gather.h's dot product).
 template <int D>
 __device__ __forceinline__ float dot_words_bf16(const float (&q)[D], const uint4 (&wv)[D / 8]) {
     float s = 0.0f;
@@ -126,37 +126,6 @@ __device__ __forceinline__ float group16_sum(float v) {
     v += step_partner<2>(v);
     v += step_partner<1>(v);
     return v;
-}
-
-// Sum of a D-vector over the 16 lanes of a team, transposed: out[u] of lane
-// tl receives the team sum of dimension 16u + tl.  Recursive halving: at the
-// step with bit m (m = 8, 4, 2, 1) a lane keeps the half of its dimensions
-// whose bit m matches its own and adds its partner's values of that half
-// (the partner has the other bit m and the same higher bits, so it kept the
-// same dimensions so far), so the step exchanges half of what is left (15
-// exchanges per 16 dimensions, against 64 for a full butterfly per
-// dimension).
-template <int N, int M>
-__device__ __forceinline__ void halve_step(const float* in, float* outv, int tl) {
-    const bool hi = (tl & M) != 0;
-#pragma unroll
-    for (int b = 0; b < N; b += 2 * M) {
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-            const float lo_v = in[b + j], hi_v = in[b + M + j];
-            const float own = hi ? hi_v : lo_v, other = hi ? lo_v : hi_v;
-            outv[b / 2 + j] = own + step_partner<M>(other);
-        }
-    }
-}
-
-template <int D>
-__device__ __forceinline__ void team_sum_transpose(const float (&acc)[D], float (&out)[D / 16], int tl) {
-    float a8[D / 2], a4[D / 4], a2[D / 8];
-    halve_step<D, 8>(acc, a8, tl);
-    halve_step<D / 2, 4>(a8, a4, tl);
-    halve_step<D / 4, 2>(a4, a2, tl);
-    halve_step<D / 8, 1>(a2, out, tl);
 }
 
 }  // namespace kmip

@@ -145,8 +145,22 @@ hipError_t launch_group_queries(const void* Q, int32_t N, int32_t H, int32_t d, 
 // or nullptr (no dropout), for this launcher and the backward ones.
 hipError_t launch_attend(const void* Q, const void* K, const void* V, const int32_t* idx,
                          const uint8_t* keep, float keep_scale, int32_t N, int32_t H, int32_t d, int32_t dv,
-                         int32_t k, float scale, const int32_t* perm, float* out, float* lse,
+                         int32_t k, float scale, const int32_t* perm, bool one_graph, float* out, float* lse,
                          hipStream_t stream);
+
+// Whether the row gathers (aggregate, coefficient pass) take one head after
+// the other instead of the query-heads as they lie.  Queries of one large
+// graph select keys from all over it, so all heads at once gather from H
+// times the rows that one does; in a batch, neighbouring queries of all heads
+// share their graph's few rows.  Where the call does not know (one_graph
+// false), a wide row or a large k speaks for a large graph.  Aggregate by
+// query-head against by head (us): 30k nodes, 4 heads, d = 32, k = 256 630 and
+// 350; 20k nodes, 4 heads, d = 128, k = 32 145 and 84; 128 small graphs, 3
+// heads, d = 32, k = 16 22 and 31.  Small N would leave partly filled
+// workgroups.
+inline bool gather_by_head(int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k, bool one_graph) {
+    return H > 1 && N >= 1024 && (one_graph || k > 128 || d > 64 || dv > 64);
+}
 
 // The backward launchers take the query/key width d and the value width dv
 // (each in {16, 32, 64}); the bucketed one needs dv == d.
