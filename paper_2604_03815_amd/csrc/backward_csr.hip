@@ -25,7 +25,6 @@
 #include "kmip_internal.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace kmip {
 namespace {
@@ -686,15 +685,18 @@ __device__ __forceinline__ int32_t wave_rank(int32_t* ctr, int32_t digit) {
 // round for 8 rounds, ranked by ballots, staged in LDS and written as runs
 // into ranges the workgroup reserves with one atomic per super-bucket.  The
 // coefficients never go to memory.
-// The query-heads are taken in the order u = h N + p, query perm[h][p] at
-// position p of head h: with perm the grouping of the queries by direction,
+// The query-heads are taken in the order u = h N + p, query perm[h][p] (p
+// without perm) at position p of head h: with perm the grouping of the queries by direction,
 // queries that share most of their keys are processed together (their key
 // and value rows are gathered while in cache) and their rows of the
 // interleaved copy, row u, lie side by side, so the reduction's gathers for
 // one key row mostly read neighbouring rows and share cache lines.  The
 // records carry u as their query row.
+// (Four waves per SIMD where that costs few spills: k <= 16 at d = 32 62 -> 58
+// us in a batch of 128 graphs, k = 128 at d = 64 737 -> 655 at 262k nodes;
+// at d = 32, k = 32 it would cost 57 spilled registers, 285 -> 485 us.)
 template <int D, int NS>
-__global__ __launch_bounds__(256) void coef_split_kernel(
+__global__ __launch_bounds__(256, NS == 8 || (NS == 1 && D == 32) ? 4 : 1) void coef_split_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const uint16_t* __restrict__ dO, const int32_t* __restrict__ idx, const float* __restrict__ lse,
     const int32_t* __restrict__ perm, int32_t N, int32_t H, int32_t k, float scale, float* __restrict__ dQ,
@@ -721,7 +723,7 @@ __global__ __launch_bounds__(256) void coef_split_kernel(
 #pragma unroll
     for (int it = 0; it < TQ; ++it) {
         const int64_t u = u0 + it * 16;
-        qrow[it] = u < nh ? perm[u] : 0;
+        qrow[it] = u >= nh ? 0 : perm != nullptr ? perm[u] : (int32_t)(u % N);
     }
     CoefIn<NS> nxt;
     coef_fetch<D, D, NS>(Q, dO, idx, lse, N, k, u0 < nh, (int64_t)qrow[0] * H + (u0 < nh ? u0 / N : 0), tl, nxt);
@@ -799,27 +801,83 @@ hipError_t launch_coef_split(int32_t nh, hipStream_t stream, const uint16_t* q, 
     return hipGetLastError();
 }
 
-// Per super-bucket: its first record (supst, nsup + 1 entries), the cursor
-// pass 1 reserves from (supcur), and the scanned number of pass-2 pieces
-// (pstart2, nsup + 1 entries).  One wave.
-__global__ __launch_bounds__(64) void bkt_split_setup_kernel(const int32_t* __restrict__ sstart, int32_t nbk,
-                                                             int32_t nsup, int32_t* __restrict__ supst,
-                                                             int32_t* __restrict__ supcur,
-                                                             int32_t* __restrict__ pstart2) {
-    const int s = threadIdx.x;
-    const int32_t a = sstart[min(s * kSupBuckets, nbk)];
-    const int32_t b = sstart[min((s + 1) * kSupBuckets, nbk)];
-    const int32_t np = s < nsup ? (b - a + kSplitChunk - 1) / kSplitChunk : 0;
-    int32_t tot;
-    const int32_t ex = wave_exclusive_sum(np, &tot);
-    if (s < nsup) {
-        supst[s] = a;
-        supcur[s] = a;
-        pstart2[s] = ex;
+constexpr int kPiece = 4096;   // records per reduction workgroup (sorted in 48 KB of LDS)
+
+// Everything that follows from the bucket counts, in one workgroup (nbk <=
+// kMaxBuckets; six scan launches and two small ones before, about 4 us each):
+//   gcnt    the counts become the buckets' first records (the cursors pass 2
+//           advances; entry nbk the total), sstart keeps a copy;
+//   pstart  scanned number of reduction pieces of at most kPiece records;
+//   supst   first record of each super-bucket (nsup + 1 entries), supcur the
+//           cursors pass 1 reserves from, pstart2 the scanned number of
+//           pass-2 pieces (nsup + 1).
+__global__ __launch_bounds__(kScanBlock) void bkt_scan_kernel(int32_t* __restrict__ gcnt, int32_t nbk, int32_t nsup,
+                                                              int32_t* __restrict__ sstart,
+                                                              int32_t* __restrict__ pstart,
+                                                              int32_t* __restrict__ supst,
+                                                              int32_t* __restrict__ supcur,
+                                                              int32_t* __restrict__ pstart2) {
+    constexpr int PER = (kMaxBuckets + kScanBlock) / kScanBlock;   // counts per thread, consecutive
+    __shared__ int32_t first[kMaxBuckets + kScanBlock];
+    __shared__ int2 wsum[kScanBlock / 64];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    int32_t c[PER], cs = 0, ps = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int b = PER * t + i;
+        c[i] = b < nbk ? gcnt[b] : 0;
+        cs += c[i];
+        ps += (c[i] + kPiece - 1) / kPiece;
     }
-    if (s == 0) {
-        supst[nsup] = sstart[nbk];
-        pstart2[nsup] = tot;
+    int32_t ctot, ptot;
+    int32_t cx = wave_exclusive_sum(cs, &ctot), px = wave_exclusive_sum(ps, &ptot);
+    if (lane == 0) wsum[wave] = make_int2(ctot, ptot);
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) {
+        cx += wsum[w].x;
+        px += wsum[w].y;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int b = PER * t + i;
+        if (b <= nbk) {
+            first[b] = cx;
+            gcnt[b] = cx;
+            sstart[b] = cx;
+            pstart[b] = px;
+        }
+        cx += c[i];
+        px += (c[i] + kPiece - 1) / kPiece;
+    }
+    __syncthreads();
+    if (t < 64) {
+        const int32_t a = first[min(t * kSupBuckets, nbk)], e = first[min((t + 1) * kSupBuckets, nbk)];
+        const int32_t np = t < nsup ? (e - a + kSplitChunk - 1) / kSplitChunk : 0;
+        int32_t tot;
+        const int32_t ex = wave_exclusive_sum(np, &tot);
+        if (t < nsup) {
+            supst[t] = a;
+            supcur[t] = a;
+            pstart2[t] = ex;
+        }
+        if (t == 0) {
+            supst[nsup] = first[nbk];
+            pstart2[nsup] = tot;
+        }
+    }
+}
+
+// Zeroes the bucket counts and both gradients (n4, m4: float4 counts; g4: int4s).
+__global__ __launch_bounds__(256) void bkt_clear_kernel(int4* __restrict__ gcnt, int64_t g4, float4* __restrict__ dK,
+                                                        int64_t n4, float4* __restrict__ dV, int64_t m4) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < g4 + n4 + m4; i += stride) {
+        if (i < n4)
+            dK[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        else if (i < n4 + m4)
+            dV[i - n4] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        else
+            gcnt[i - n4 - m4] = make_int4(0, 0, 0, 0);
     }
 }
 
@@ -891,76 +949,52 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
     }
 }
 
-constexpr int kPiece = 8192;   // records per reduction workgroup (fits a uint16 order)
-
-// After the scan: the start of each bucket's records (kept; the place pass
-// moves the cursors) and its number of pieces of at most kPiece records.
-__global__ __launch_bounds__(256) void bkt_pieces_kernel(const int32_t* __restrict__ start, int32_t nbk,
-                                                         int32_t* __restrict__ sstart,
-                                                         int32_t* __restrict__ npieces) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b > nbk) return;
-    sstart[b] = start[b];
-    if (b < nbk) npieces[b] = (start[b + 1] - start[b] + kPiece - 1) / kPiece;
-    else npieces[b] = 0;
-}
-
-// One workgroup per piece (a stretch of at most kPiece records of one
-// bucket, found by binary search in the scanned piece counts):
-//   1. counting sort of the piece's records by key row in LDS (claim_slot:
+// The reduction of a piece (a stretch of at most kPiece records of one bucket,
+// found by binary search in the scanned piece counts), one workgroup of 512
+// threads:
+//   1. counting sort of the piece's records by key row into LDS (claim_slot:
 //      a key most pairs share costs about one LDS atomic per wave);
-//   2. sixteen teams of 16 lanes walk contiguous stretches of the sorted
-//      order.  A record's query row of the interleaved head-major copy
-//      (q then dO, 4d bytes) is one load per team, lane tl taking d/8
-//      elements: lanes 0-7 hold q and add a*q to dK, lanes 8-15 hold dO and
-//      add p*dO to dV.  Head-major rows let a key's run of queries of one
-//      head read consecutive rows.  A team keeps the sums of the current key
-//      row in registers and adds them to dK and dV (zero at the start) with
-//      one atomic per dimension where the row changes or the stretch ends; it
-//      loads the rows of eight pairs before adding them up.
-template <int E>
-struct RowChunk;   // E bf16 values, one load
-template <> struct RowChunk<2> { uint32_t w[1]; };
-template <> struct RowChunk<4> { uint32_t w[2]; };
-template <> struct RowChunk<8> { uint32_t w[4]; };
+//   2. LG = D/4 lanes take a contiguous span of the sorted records.  A record's
+//      query row of the interleaved head-major copy (q then dO, 4d bytes) is
+//      one 16-byte load per lane; the first half of the lanes add a*q to dK,
+//      the second p*dO to dV, eight records' rows in flight.  A key row whose
+//      records all lie in the span is stored (added with atomics where the
+//      bucket has several pieces); the row a span starts in the middle of and
+//      the one it ends in go to LDS;
+//   3. these partial rows, in row order, are added up sixteen at a time, an
+//      atomic per element where the row changes (dK and dV are zero at the
+//      start).
+// Bound by the fabric on the row gathers of large problems, by the chain of
+// phases of a workgroup on small ones.  Against sixteen-lane teams on 8192
+// records that added every run with atomics (us): 128 graphs, d = 32, k = 16
+// 117 -> 46; 16 clouds, d = 32, k = 32 178 -> 87; 100k nodes, d = 32 480 -> 321;
+// 262k nodes, d = 64, k = 128 1605 -> 1155; 500k nodes, d = 16 1072 -> 1115.
+// (Sums in LDS with float atomics instead of the sort were six times slower:
+// an LDS float add took about four clocks a lane.)
+constexpr int kSumThreads = 512;
 
-template <int E>
-__device__ __forceinline__ RowChunk<E> load_chunk(const uint16_t* p) {
-    RowChunk<E> c;
-    if constexpr (E == 2) {
-        c.w[0] = *reinterpret_cast<const uint32_t*>(p);
-    } else if constexpr (E == 4) {
-        const uint2 v = *reinterpret_cast<const uint2*>(p);
-        c.w[0] = v.x;
-        c.w[1] = v.y;
-    } else {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        c.w[0] = v.x;
-        c.w[1] = v.y;
-        c.w[2] = v.z;
-        c.w[3] = v.w;
-    }
-    return c;
-}
-
-template <int D, int RB>
-__global__ __launch_bounds__(256) void bkt_reduce_kernel(const uint16_t* __restrict__ QG,
-                                                         const BucketRecord* __restrict__ rec,
-                                                         const int32_t* __restrict__ sstart,
-                                                         const int32_t* __restrict__ pstart, int32_t nbk,
-                                                         float* __restrict__ dK, float* __restrict__ dV) {
-    constexpr int E = D / 8;            // elements of the interleaved row per lane
-    constexpr int G = 8;                // pairs whose rows a team loads at once
-    constexpr int CPT = (RB + 255) / 256;   // cursors per thread in the scan
-    using LRow = typename std::conditional<(RB <= 256), uint8_t, uint16_t>::type;
-    __shared__ uint16_t ord[kPiece];
-    __shared__ LRow lrow[kPiece];
-    __shared__ int32_t cursor[RB];
-    __shared__ int32_t sh[256];
+template <int D>
+__global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t* __restrict__ QG,
+                                                                 const BucketRecord* __restrict__ rec,
+                                                                 const int32_t* __restrict__ sstart,
+                                                                 const int32_t* __restrict__ pstart, int32_t nbk,
+                                                                 int32_t shift, float* __restrict__ dK,
+                                                                 float* __restrict__ dV) {
+    constexpr int LG = D / 4;                  // lanes per record
+    constexpr int GR = kSumThreads / LG;       // lane groups
+    constexpr int B = 4;                       // records of a group in flight
+    constexpr int PER = kPiece / kSumThreads;  // records per thread in the sort
+    constexpr int SEG = 16;                    // partial rows summed by one thread
+    static_assert(2 * GR * D * 2 * sizeof(float) <= kPiece * sizeof(BucketRecord), "partial rows fit the records' area");
+    static_assert(kSumThreads / (2 * D) * SEG == 2 * GR, "every partial row has its threads");
+    static_assert(kMaxBucketRows <= kSumThreads, "one counter a thread in the scan");
+    __shared__ BucketRecord srt[kPiece];
+    __shared__ int32_t base[kMaxBucketRows + 1];
+    __shared__ int32_t wsum[kSumThreads / 64];
+    __shared__ int32_t prow[2 * GR];
     const int t = threadIdx.x;
     const int w = blockIdx.x;
     if (w >= pstart[nbk]) return;
-    // bucket b with pstart[b] <= w < pstart[b + 1]
     int lo = 0, hi = nbk;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -968,126 +1002,127 @@ __global__ __launch_bounds__(256) void bkt_reduce_kernel(const uint16_t* __restr
     }
     const int32_t e0 = sstart[lo] + (w - pstart[lo]) * kPiece;
     const int32_t n = min(sstart[lo + 1] - e0, kPiece);
-    for (int r = t; r < RB; r += 256) cursor[r] = 0;
+    const bool alone = pstart[lo + 1] - pstart[lo] == 1;
+    const int rb = 1 << shift;
+    if (t < rb) base[t] = 0;
+    for (int i = t; i < 2 * GR; i += kSumThreads) prow[i] = -1;
     __syncthreads();
 
-    // 1a. records per key row; the rows (local to the bucket) are kept in LDS
-    for (int base = 0; base < n; base += 1024) {
-        int32_t row[4];
+    // 1. sort by key row
+    BucketRecord r[PER];
+    int32_t slot[PER];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + 256 * u + t;
-            row[u] = i < n ? (int32_t)(rec[e0 + i].packed >> kQRowBits) : -1;
-        }
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * kSumThreads + t;
+        r[u] = BucketRecord{0u, 0.0f, 0.0f};
+        if (i < n) r[u] = rec[e0 + i];
+    }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + 256 * u + t;
-            if (row[u] >= 0) lrow[i] = (LRow)row[u];
-            claim_slot<false>(cursor, row[u]);
-        }
+    for (int u = 0; u < PER; ++u) {
+        slot[u] = 0;
+        if (u * kSumThreads < n)
+            slot[u] = claim_slot<true>(base, u * kSumThreads + t < n ? (int32_t)(r[u].packed >> kQRowBits) : -1);
     }
     __syncthreads();
-    // 1b. exclusive scan of the counts: the cursors (thread t owns cursors
-    // CPT t .. CPT t + CPT - 1)
-    int32_t c = 0;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) c += CPT * t + j < RB ? cursor[CPT * t + j] : 0;
-    sh[t] = c;
+    const int32_t mine = t < rb ? base[t] : 0;
+    int32_t tot;
+    int32_t ex = wave_exclusive_sum(mine, &tot);
+    if ((t & 63) == 0) wsum[t >> 6] = tot;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int32_t add = t >= off ? sh[t - off] : 0;
-        __syncthreads();
-        sh[t] += add;
-        __syncthreads();
-    }
-    int32_t run = sh[t] - c;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-        if (CPT * t + j < RB) {
-            const int32_t v = cursor[CPT * t + j];
-            cursor[CPT * t + j] = run;
-            run += v;
-        }
-    }
+    for (int v = 0; v < (t >> 6); ++v) ex += wsum[v];
+    if (t < rb) base[t] = ex;
+    if (t == rb - 1) base[rb] = n;
     __syncthreads();
-    // 1c. place the record numbers in key-row order
-    for (int base = 0; base < n; base += 256) {
-        const int i = base + t;
-        const int32_t row = i < n ? (int32_t)lrow[i] : -1;
-        const int32_t slot = claim_slot<true>(cursor, row);
-        if (row >= 0) ord[slot] = (uint16_t)i;
-    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (u * kSumThreads + t < n) srt[base[r[u].packed >> kQRowBits] + slot[u]] = r[u];
     __syncthreads();
 
-    // 2. teams walk the sorted order
-    const int tl = t & 15;
-    const int team = t >> 4;
-    const bool isq = tl < 8;
-    const int span = (n + 15) / 16;
-    const int p0 = min(n, team * span), p1 = min(n, p0 + span);
-    int32_t cur = -1;
-    float acc[E];
+    // 2. spans of the sorted records
+    const int c = t & (LG - 1), grp = t / LG;
+    const bool isq = c < LG / 2;
+    const uint16_t* const col = QG + 8 * c;
+    float* const dst = (isq ? dK : dV) + ((size_t)lo << shift) * D + 8 * (c & (LG / 2 - 1));
+    const int span = ((n + GR - 1) / GR) | 1;   // odd: the groups' 12-byte records start in different banks
+    const int p0 = min(n, grp * span), p1 = min(n, p0 + span);
+    int32_t cur = -1, row0 = -1, row1 = -1;   // current row; rows of the span's partial sums
+    float acc[8], acc0[8];                    // current sums; those of the row the span starts inside of
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-    float* const dst0 = (isq ? dK : dV) + (tl & 7) * E;
+    for (int e = 0; e < 8; ++e) acc[e] = acc0[e] = 0.0f;
     auto flush = [&]() {
         if (cur >= 0) {
+            const int32_t f0 = base[cur], f1 = base[cur + 1];
+            if (f0 < p0) {
+                row0 = cur;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                atomicAdd(dst0 + (size_t)cur * D + e, acc[e]);
-                acc[e] = 0.0f;
+                for (int e = 0; e < 8; ++e) acc0[e] = acc[e];
+            } else if (f1 > p1) {
+                row1 = cur;   // the last row: its sums stay in acc
+                return;
+            } else if (alone) {
+                float4* d4 = reinterpret_cast<float4*>(dst + (size_t)cur * D);
+                d4[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                d4[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) atomicAdd(dst + (size_t)cur * D + e, acc[e]);
             }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
         }
     };
-    const int32_t row0 = lo * RB;   // first key row of the bucket
-    BucketRecord next{0u, 0.0f, 0.0f};
-    if (p0 + tl < p1) next = rec[e0 + ord[p0 + tl]];
-    for (int pb = p0; pb < p1; pb += 16) {
-        const BucketRecord r = next;   // this batch's records; the next batch's are fetched now
-        next = BucketRecord{0u, 0.0f, 0.0f};
-        if (pb + 16 + tl < p1) next = rec[e0 + ord[pb + 16 + tl]];
-        const int m = min(16, p1 - pb);
-        for (int s0 = 0; s0 < m; s0 += G) {
-            int32_t rt[G];
-            float ct[G];
-            RowChunk<E> rv[G];
+    for (int i0 = p0; i0 < p1; i0 += B) {
+        BucketRecord rr[B];
+        uint4 x[B];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const uint32_t pk = (uint32_t)__shfl((int32_t)r.packed, s0 + g, 16);
-                rt[g] = row0 + (int32_t)(pk >> kQRowBits);
-                const int32_t qt = (int32_t)(pk & ((1u << kQRowBits) - 1u));
-                // lanes 0-7 take the record's a, lanes 8-15 its p
-                const float ca = __shfl(r.a, s0 + g, 16), cp = __shfl(r.p, s0 + g, 16);
-                ct[g] = isq ? ca : cp;
-                if (s0 + g < m) {
-                    rv[g] = load_chunk<E>(QG + (size_t)qt * (2 * D) + tl * E);
-                } else {
+        for (int b = 0; b < B; ++b) {
+            rr[b] = srt[min(i0 + b, p1 - 1)];
+            x[b] = *reinterpret_cast<const uint4*>(col + (size_t)(rr[b].packed & ((1u << kQRowBits) - 1u)) * (2 * D));
+        }
 #pragma unroll
-                    for (int w = 0; w < E / 2; ++w) rv[g].w[w] = 0u;
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (s0 + g >= m) break;
-                if (rt[g] != cur) {
+        for (int b = 0; b < B; ++b) {
+            if (i0 + b < p1) {
+                const int32_t row = (int32_t)(rr[b].packed >> kQRowBits);
+                if (row != cur) {
                     flush();
-                    cur = rt[g];
+                    cur = row;
                 }
-#pragma unroll
-                for (int w = 0; w < E / 2; ++w) {
-                    acc[2 * w] = fmaf(ct[g], bf16_bits_to_f32(rv[g].w[w] & 0xFFFFu), acc[2 * w]);
-                    acc[2 * w + 1] = fmaf(ct[g], bf16_bits_to_f32(rv[g].w[w] >> 16), acc[2 * w + 1]);
-                }
+                const float ca = rr[b].a, cp = rr[b].p;
+                axpy8(acc, isq ? ca : cp, x[b]);
             }
         }
     }
     flush();
-}
+    __syncthreads();   // every record has been read: partial rows take their place
+    float* const part = reinterpret_cast<float*>(srt);   // [2 GR][2 D]
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const int32_t row = side == 0 ? row0 : row1;
+        if (row >= 0) {
+            float* d8 = part + (size_t)(2 * grp + side) * (2 * D) + 8 * c;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d8[e] = side == 0 ? acc0[e] : acc[e];
+            if (c == 0) prow[2 * grp + side] = row;
+        }
+    }
+    __syncthreads();
 
-// perm[h][p] = p: the plain query order, in the layout of a grouping.
-__global__ __launch_bounds__(256) void identity_order_kernel(int32_t N, int32_t H, int32_t* __restrict__ perm) {
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (u < (int64_t)N * H) perm[u] = (int32_t)(u % N);
+    // 3. partial rows, an element a thread
+    const int el = t % (2 * D), sg = t / (2 * D);
+    float* const out = (el < D ? dK : dV) + ((size_t)lo << shift) * D + (el < D ? el : el - D);
+    int32_t at = -1;
+    float v = 0.0f;
+    for (int i = sg * SEG; i < sg * SEG + SEG; ++i) {
+        const int32_t row = prow[i];
+        if (row < 0) continue;
+        if (row != at) {
+            if (at >= 0) atomicAdd(out + (size_t)at * D, v);
+            at = row;
+            v = 0.0f;
+        }
+        v += part[(size_t)i * (2 * D) + el];
+    }
+    if (at >= 0) atomicAdd(out + (size_t)at * D, v);
 }
 
 }  // namespace
@@ -1132,7 +1167,6 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     p += al(((size_t)nbk + 1) * sizeof(int32_t));
     int32_t* pstart = reinterpret_cast<int32_t*>(p);   // pieces per bucket, then their starts
     p += al(((size_t)nbk + 1) * sizeof(int32_t));
-    int32_t* sums = reinterpret_cast<int32_t*>(p);
     p += al(((size_t)nb + 1) * sizeof(int32_t));
     uint16_t* qg = reinterpret_cast<uint16_t*>(p);   // q and dO interleaved, row h N + p for query perm[h][p]
     p += al((size_t)nh * 2 * d * sizeof(uint16_t));
@@ -1156,51 +1190,25 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     // (measured: 2^24 pairs and more; below, the plain order is as fast or
     // faster, 14% at 1.7M pairs in a batch of small graphs).
     QueryGroups groups{};
-    if ((int64_t)pairs >= (int64_t(1) << 24)) {
-        if ((e = launch_group_queries(Q, N, H, d, gws, &groups, stream)) != hipSuccess) return e;
-    } else {
-        int32_t* order = reinterpret_cast<int32_t*>(gws);
-        groups.perm = order;
-        hipLaunchKernelGGL(identity_order_kernel, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, stream, N, H,
-                           order);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if ((e = launch_fill_zero(reinterpret_cast<float*>(gcnt), ((size_t)nbk + 1 + 3) / 4 * 4, stream)) != hipSuccess)
+    if ((int64_t)pairs >= (int64_t(1) << 24) &&
+        (e = launch_group_queries(Q, N, H, d, gws, &groups, stream)) != hipSuccess)
         return e;
-    if ((e = launch_fill_zero(dK, (size_t)nh * d, stream)) != hipSuccess) return e;
-    if ((e = launch_fill_zero(dV, (size_t)nh * d, stream)) != hipSuccess) return e;
-    // pairs per counting workgroup: about 1024 workgroups, 8192 .. 65536 pairs each
-    const uint32_t per = (uint32_t)std::min<size_t>(65536, std::max<size_t>(8192, (pairs / 1024 + 255) / 256 * 256));
+    const int64_t g4 = ((int64_t)nbk + 1 + 3) / 4, n4 = nh * d / 4;
+    const unsigned zblocks = (unsigned)std::min<int64_t>((g4 + 2 * n4 + 255) / 256, 256 * 32);
+    hipLaunchKernelGGL(bkt_clear_kernel, dim3(zblocks), dim3(256), 0, stream, reinterpret_cast<int4*>(gcnt), g4,
+                       reinterpret_cast<float4*>(dK), n4, reinterpret_cast<float4*>(dV), n4);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // pairs per counting workgroup: about 1024 workgroups, 2048 .. 65536 pairs
+    // each (1.7M pairs in 209 workgroups of 8192 took 32 us)
+    const uint32_t per = (uint32_t)std::min<size_t>(65536, std::max<size_t>(2048, (pairs / 1024 + 255) / 256 * 256));
     const unsigned cblocks = (unsigned)((pairs + per - 1) / per);
     const FastDiv divk = make_fastdiv((uint32_t)k), divh = make_fastdiv((uint32_t)H);
     hipLaunchKernelGGL(bkt_count_kernel, dim3(cblocks), dim3(256), 0, stream, idx, N, H, k, divk, divh, shift,
                        nbk, per, gcnt);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // exclusive scan of the nbk counts; gcnt[nbk] (zero) becomes the total
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, gcnt,
-                       (int64_t)nbk + 1, sums);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanBlock), 0, stream, sums, nb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, gcnt,
-                       (int64_t)nbk + 1, sums);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // keep the starts, count the pieces and scan them
-    hipLaunchKernelGGL(bkt_pieces_kernel, dim3((unsigned)((nbk + 1 + 255) / 256)), dim3(256), 0, stream, gcnt,
-                       nbk, sstart, pstart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, pstart,
-                       (int64_t)nbk + 1, sums);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanBlock), 0, stream, sums, nb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, stream, pstart,
-                       (int64_t)nbk + 1, sums);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the two split passes; pass 2 advances each bucket's start to its end
     const int32_t nsup = (nbk + kSupBuckets - 1) / kSupBuckets;
-    hipLaunchKernelGGL(bkt_split_setup_kernel, dim3(1), dim3(64), 0, stream, sstart, nbk, nsup, supst, supcur,
-                       pstart2);
+    hipLaunchKernelGGL(bkt_scan_kernel, dim3(1), dim3(kScanBlock), 0, stream, gcnt, nbk, nsup, sstart, pstart, supst,
+                       supcur, pstart2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // coefficients, dQ and the interleaved copy, fused with placement pass 1
     if (d == 16)
@@ -1218,19 +1226,13 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // at most one piece per bucket plus one per kPiece pairs; the rest exit
     const unsigned rblocks = (unsigned)(nbk + (pairs + kPiece - 1) / kPiece);
-#define KMIP_BKT_REDUCE(DD, RBV)                                                                       \
-    if (d == DD && rb == RBV)                                                                          \
-        hipLaunchKernelGGL((bkt_reduce_kernel<DD, RBV>), dim3(rblocks), dim3(256), 0, stream, qg, rec, sstart, \
-                           pstart, nbk, dK, dV);
-    KMIP_BKT_REDUCE(16, 256)
-    KMIP_BKT_REDUCE(16, 512)
-    KMIP_BKT_REDUCE(32, 128)
-    KMIP_BKT_REDUCE(32, 256)
-    KMIP_BKT_REDUCE(32, 512)
-    KMIP_BKT_REDUCE(64, 64)
-    KMIP_BKT_REDUCE(64, 128)
-    KMIP_BKT_REDUCE(64, 256)
-    KMIP_BKT_REDUCE(64, 512)
+#define KMIP_BKT_REDUCE(DD)                                                                                    \
+    if (d == DD)                                                                                               \
+        hipLaunchKernelGGL(bkt_reduce_kernel<DD>, dim3(rblocks), dim3(kSumThreads), 0, stream, qg, rec, sstart, \
+                           pstart, nbk, shift, dK, dV);
+    KMIP_BKT_REDUCE(16)
+    KMIP_BKT_REDUCE(32)
+    KMIP_BKT_REDUCE(64)
 #undef KMIP_BKT_REDUCE
     return hipGetLastError();
 }
