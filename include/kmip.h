@@ -229,14 +229,16 @@ kmip_status_t kmip_fwd_ex_with_events(const void* Q, const void* K, const void* 
  *            KMIP_BWD_BUCKETED: the pairs are counting-sorted by buckets of
  *                consecutive key rows (j*H + h), 4096/d of them, doubled up
  *                to 512 while N*H would need more than 8192 buckets; each
- *                bucket's records are sorted by key row in LDS, at most 8192
- *                at a time, and reduced as in SEGMENTED; needs
+ *                bucket's records are sorted by key row in LDS, at most 4096
+ *                at a time, and each row summed in registers; needs
  *                N*H <= 8192*512, d <= 64 and k <= 128 (else
  *                KMIP_ERR_UNSUPPORTED and workspace size 0);
  *            KMIP_BWD_KEY_AGGREGATED: queries are grouped by direction, each
  *                workgroup of 256 queries sums its pairs per key in LDS and
  *                adds each key's sums once;
- *            KMIP_BWD_AUTO: BUCKETED where it is supported, else SEGMENTED;
+ *            KMIP_BWD_AUTO: BUCKETED where it is supported, else SEGMENTED
+ *                (or, for more than 2^20 pairs, the bucketed reduction in its
+ *                form for d = 128 and k > 128);
  *            any other value: KMIP_ERR_UNSUPPORTED.
  *   workspace: kmip_bwd_workspace_size(variant) bytes, 256-byte aligned
  *              (0 for KMIP_BWD_ATOMIC, which accepts NULL); too small or
@@ -265,7 +267,9 @@ kmip_status_t kmip_bwd(const void* Q, const void* K, const void* V, const void* 
  * p_j f_j dOut_i and f_j dp_j replaces dp_j in D_i and g_j).
  * KMIP_BWD_BUCKETED needs dv == d (else KMIP_ERR_UNSUPPORTED and workspace
  * size 0): its interleaved copy of q_i and dOut_i assumes equal widths;
- * KMIP_BWD_AUTO then picks KMIP_BWD_SEGMENTED.  kmip_bwd and
+ * KMIP_BWD_AUTO then runs the bucketed reduction in its form for unequal
+ * widths, while N*H <= 8192*512, or KMIP_BWD_SEGMENTED where the workspace
+ * passed holds only that one's arrays.  kmip_bwd and
  * kmip_bwd_workspace_size are the case dv = d, keep = NULL.
  */
 size_t kmip_bwd_ex_workspace_size(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k, int32_t variant);

@@ -537,18 +537,38 @@ kmip_status_t kmip_fwd(const void* Q, const void* K, const void* V, const int32_
 
 // Backward variant the library picks (KMIP_BWD_AUTO): the bucketed reduction
 // where the key rows fit its bucket table, the sizes are its own and the
-// value width equals the key width, else the full key sort.
+// value width equals the key width, else the full key sort (for which the
+// bucketed reduction may stand in, see wide_buckets).
 static int32_t default_bwd_variant(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k) {
     return dv == d && kmip::bwd_bucket_supported((int32_t)N, H, d, k) ? KMIP_BWD_BUCKETED : KMIP_BWD_SEGMENTED;
+}
+
+// Whether KMIP_BWD_AUTO runs the bucketed reduction where it would pick the
+// key sort (unequal widths, d = 128, k > 128): its workspace is larger
+// (28 against 24 bytes a pair, and the interleaved query rows), and a caller
+// whose workspace holds only the key sort's gets that.  With equal widths and
+// up to 2^20 pairs the key sort, and its smaller workspace, stay (there its
+// passes over the index rows, uncoalesced for a large k, cost little).  Whole
+// backward, key sort against buckets (us): 1,500 nodes, 3 heads, d = 32, d_V =
+// 64, k = 16 149 and 76; 60,000 nodes of the same 359 and 305; 10,000 nodes, 4
+// heads, d = 128, k = 32 404 and 262; 3,000 nodes, 2 heads, d = 32, k = 256
+// 1066 and 157; 30,000 nodes, 2 heads, d = 128, k = 100 1512 and 1391.
+static bool wide_buckets(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k) {
+    const int64_t pairs = N * (int64_t)H * k;
+    return default_bwd_variant(N, H, d, dv, k) == KMIP_BWD_SEGMENTED && (dv != d || pairs > (1 << 20)) &&
+           kmip::bwd_bucket_rows((int32_t)N, H, d);
 }
 
 size_t kmip_bwd_ex_workspace_size(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k, int32_t variant) {
     if (check_sizes(N, H, d, k) != KMIP_OK || check_value_width(N, H, dv) != KMIP_OK) return 0;
     const int32_t v = variant == KMIP_BWD_AUTO ? default_bwd_variant(N, H, d, dv, k) : variant;
     if (v == KMIP_BWD_KEY_AGGREGATED) return align_up(kmip::bwd_agg_workspace_bytes((int32_t)N, H, d));
+    if (variant == KMIP_BWD_AUTO && wide_buckets(N, H, d, dv, k))
+        return std::max(align_up(kmip::bwd_bucket_workspace_bytes((int32_t)N, H, d, dv, k)),
+                        align_up(kmip::bwd_csr_workspace_bytes((int32_t)N, H, k)));
     if (v == KMIP_BWD_SEGMENTED) return align_up(kmip::bwd_csr_workspace_bytes((int32_t)N, H, k));
     if (v == KMIP_BWD_BUCKETED) return dv == d && kmip::bwd_bucket_supported((int32_t)N, H, d, k)
-                                         ? align_up(kmip::bwd_bucket_workspace_bytes((int32_t)N, H, d, k))
+                                         ? align_up(kmip::bwd_bucket_workspace_bytes((int32_t)N, H, d, dv, k))
                                          : 0;
     return 0;
 }
@@ -591,12 +611,16 @@ kmip_status_t kmip_bwd_ex(const void* Q, const void* K, const void* V, const voi
     if (v == KMIP_BWD_KEY_AGGREGATED) {
         e = kmip::launch_bwd_agg(Q, K, V, dOut, topk_idx, lse, keep, keep_scale, (int32_t)N, H, d, dv, k, scale,
                                  dQ, dK, dV, workspace, stream);
+    } else if (variant == KMIP_BWD_AUTO && wide_buckets(N, H, d, dv, k) &&
+               workspace_bytes >= kmip::bwd_bucket_workspace_bytes((int32_t)N, H, d, dv, k)) {
+        e = kmip::launch_bwd_bucket(Q, K, V, dOut, topk_idx, lse, keep, keep_scale, (int32_t)N, H, d, dv, k, scale,
+                                    dQ, dK, dV, workspace, stream);
     } else if (v == KMIP_BWD_BUCKETED) {
         if (!kmip::bwd_bucket_supported((int32_t)N, H, d, k))
             return record_error(KMIP_ERR_UNSUPPORTED,
                                 "the bucketed variant needs d <= 64, k <= 128 and N*H <= 8192*512 (key-row "
                                 "buckets of at most 512 rows)");
-        e = kmip::launch_bwd_bucket(Q, K, V, dOut, topk_idx, lse, keep, keep_scale, (int32_t)N, H, d, k, scale,
+        e = kmip::launch_bwd_bucket(Q, K, V, dOut, topk_idx, lse, keep, keep_scale, (int32_t)N, H, d, dv, k, scale,
                                     dQ, dK, dV, workspace, stream);
     } else if (v == KMIP_BWD_SEGMENTED) {
         e = kmip::launch_bwd_csr(Q, K, V, dOut, topk_idx, lse, keep, keep_scale, (int32_t)N, H, d, dv, k, scale,

@@ -33,8 +33,8 @@ constexpr int kScanBlock = 1024;     // counts per block of the scan
 constexpr int kChunk = 1024;         // sorted pairs per wave in the reduction
 
 // 1. Per (query, head), a team of 16 lanes, NS slots per lane (k <= 16 NS):
-// p, dp, D, g of each selected pair, dQ_i, and (QGt != nullptr, value width
-// DV = D only) row qg_row of the interleaved copy of q_i and dO_i.  D is the
+// p, dp, D, g of each selected pair, dQ_i, and (QGt != nullptr) row qg_row of
+// the interleaved copy of q_i and dO_i.  D is the
 // query/key width, DV the value width (dp_j runs over it).  Slot tl + 16 s
 // leaves its key index in jj[s] (-1: none) and its coefficients a = scale g, p
 // in ca[s], cp[s].  With attention dropout (keep != nullptr, f = keep_scale or
@@ -101,15 +101,12 @@ __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* 
     int32_t* const js = reinterpret_cast<int32_t*>(sd + K16);  // [K16]
     const int64_t qh = in.qh;
     const int h = (int)(qh % H);
-    if constexpr (DV == D) {
+    if (QGt != nullptr && in.valid) {
         // row qg_row of the interleaved copy, q_i then dO_i, so that the
         // reduction gathers both with one load
-        if (QGt != nullptr && in.valid && tl < 2 * KS::LPR) {
-            const bool isq = tl < KS::LPR;   // (by component: a select of the two keeps them in memory)
-            reinterpret_cast<uint4*>(QGt + qg_row * (2 * D))[tl] =
-                make_uint4(isq ? in.qw.x : in.gw.x, isq ? in.qw.y : in.gw.y, isq ? in.qw.z : in.gw.z,
-                           isq ? in.qw.w : in.gw.w);
-        }
+        uint4* const row = reinterpret_cast<uint4*>(QGt + qg_row * (D + DV));
+        if (tl < KS::LPR) row[tl] = in.qw;
+        if (tl < VS::LPR) row[KS::LPR + tl] = in.gw;
     }
     float q[8], g[8];
     widen8(q, in.qw);
@@ -684,7 +681,9 @@ __device__ __forceinline__ int32_t wave_rank(int32_t* ctr, int32_t digit) {
 // writes their records in super-bucket order: one record per lane and
 // round for 8 rounds, ranked by ballots, staged in LDS and written as runs
 // into ranges the workgroup reserves with one atomic per super-bucket.  The
-// coefficients never go to memory.
+// coefficients never go to memory.  (k > 128: a team's LDS area is large, so
+// the workgroup has 8 or 4 teams of one query-head each, and the records go
+// out in NS / 8 chunks.)
 // The query-heads are taken in the order u = h N + p, query perm[h][p] (p
 // without perm) at position p of head h: with perm the grouping of the queries by direction,
 // queries that share most of their keys are processed together (their key
@@ -695,50 +694,54 @@ __device__ __forceinline__ int32_t wave_rank(int32_t* ctr, int32_t digit) {
 // (Four waves per SIMD where that costs few spills: k <= 16 at d = 32 62 -> 58
 // us in a batch of 128 graphs, k = 128 at d = 64 737 -> 655 at 262k nodes;
 // at d = 32, k = 32 it would cost 57 spilled registers, 285 -> 485 us.)
-template <int D, int NS>
-__global__ __launch_bounds__(256, NS == 8 || (NS == 1 && D == 32) ? 4 : 1) void coef_split_kernel(
+constexpr int split_threads(int ns) { return ns <= 8 ? 256 : 2048 / ns; }
+
+template <int D, int DV, int NS>
+__global__ __launch_bounds__(split_threads(NS), D <= 64 && (NS == 8 || (NS == 1 && D == 32)) ? 4 : 1) void coef_split_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const uint16_t* __restrict__ dO, const int32_t* __restrict__ idx, const float* __restrict__ lse,
     const int32_t* __restrict__ perm, int32_t N, int32_t H, int32_t k, float scale, float* __restrict__ dQ,
     uint16_t* __restrict__ QGt, int32_t shift, int32_t* __restrict__ supcur, PairRecord* __restrict__ mid,
     const uint8_t* __restrict__ keep, float keep_scale) {
-    constexpr int TQ = 8 / NS;   // query-heads per team
-    constexpr int R = TQ * NS;   // records per lane: 8
-    static_assert(256 * R == kSplitChunk, "one staging chunk per workgroup");
+    constexpr int THREADS = split_threads(NS), TEAMS = THREADS / 16;
+    constexpr int TQ = NS <= 8 ? 8 / NS : 1;   // query-heads per team
+    constexpr int R = 8;                       // records per lane and chunk
+    constexpr int CHUNKS = TQ * NS / R;
+    constexpr size_t kStage = THREADS * R * sizeof(PairRecord), kAreas = TEAMS * coef_area(NS);
     __shared__ int32_t cnt[kMaxSup], lstart[kMaxSup], gbase[kMaxSup];
-    __shared__ PairRecord stage[kSplitChunk];   // the teams' areas before
-    static_assert(16 * coef_area(NS) <= sizeof(stage), "the areas fit the staging chunk");
+    __shared__ uint4 lds[(kStage > kAreas ? kStage : kAreas) / 16];   // the teams' areas, then the staged chunk
+    PairRecord* const stage = reinterpret_cast<PairRecord*>(lds);
     __shared__ int32_t total;
     const int t = threadIdx.x;
     const int tl = t & 15, team = t >> 4;
     const int64_t nh = (int64_t)N * H;
-    if (t < kMaxSup) cnt[t] = 0;
-    char* const area = reinterpret_cast<char*>(stage) + team * coef_area(NS);
-    PairRecord rr[R];
-    int32_t sup[R], slot[R];
+    for (int i = t; i < kMaxSup; i += THREADS) cnt[i] = 0;
+    char* const area = reinterpret_cast<char*>(lds) + team * coef_area(NS);
+    PairRecord rr[CHUNKS * R];
+    int32_t sup[CHUNKS * R];
     // the query rows of a team first, then each query-head's inputs while the
     // one before computes
-    const int64_t u0 = (int64_t)blockIdx.x * (16 * TQ) + team;
+    const int64_t u0 = (int64_t)blockIdx.x * (TEAMS * TQ) + team;
     int32_t qrow[TQ];
 #pragma unroll
     for (int it = 0; it < TQ; ++it) {
-        const int64_t u = u0 + it * 16;
+        const int64_t u = u0 + it * TEAMS;
         qrow[it] = u >= nh ? 0 : perm != nullptr ? perm[u] : (int32_t)(u % N);
     }
     CoefIn<NS> nxt;
-    coef_fetch<D, D, NS>(Q, dO, idx, lse, N, k, u0 < nh, (int64_t)qrow[0] * H + (u0 < nh ? u0 / N : 0), tl, nxt);
+    coef_fetch<D, DV, NS>(Q, dO, idx, lse, N, k, u0 < nh, (int64_t)qrow[0] * H + (u0 < nh ? u0 / N : 0), tl, nxt);
 #pragma unroll
     for (int it = 0; it < TQ; ++it) {
-        const int64_t u = u0 + it * 16;
+        const int64_t u = u0 + it * TEAMS;
         const int32_t h = u < nh ? (int32_t)(u / N) : 0;
         int32_t jj[NS];
         float ca[NS], cp[NS];
         const CoefIn<NS> cur = nxt;
         if (it + 1 < TQ) {
-            const int64_t v = u + 16;
-            coef_fetch<D, D, NS>(Q, dO, idx, lse, N, k, v < nh, (int64_t)qrow[it + 1] * H + (v < nh ? v / N : 0), tl, nxt);
+            const int64_t v = u + TEAMS;
+            coef_fetch<D, DV, NS>(Q, dO, idx, lse, N, k, v < nh, (int64_t)qrow[it + 1] * H + (v < nh ? v / N : 0), tl, nxt);
         }
-        coef_team<D, D, NS>(cur, K, V, keep, keep_scale, H, k, scale, tl, area, dQ, QGt, (size_t)u, jj, ca, cp);
+        coef_team<D, DV, NS>(cur, K, V, keep, keep_scale, H, k, scale, tl, area, dQ, QGt, (size_t)u, jj, ca, cp);
 #pragma unroll
         for (int s2 = 0; s2 < NS; ++s2) {
             const int r = it * NS + s2;
@@ -753,52 +756,60 @@ __global__ __launch_bounds__(256, NS == 8 || (NS == 1 && D == 32) ? 4 : 1) void 
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) slot[r] = wave_rank<6>(cnt, sup[r]);
-    __syncthreads();
-    if (t < 64) {
-        const int32_t c = t < kMaxSup ? cnt[t] : 0;
-        int32_t tot;
-        const int32_t ex = wave_exclusive_sum(c, &tot);
-        if (t < kMaxSup) {
+    for (int ch = 0; ch < CHUNKS; ++ch) {
+        int32_t slot[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) slot[r] = wave_rank<6>(cnt, sup[ch * R + r]);
+        __syncthreads();
+        if (t < 64) {
+            const int32_t c = cnt[t];
+            int32_t tot;
+            const int32_t ex = wave_exclusive_sum(c, &tot);
             lstart[t] = ex;
             gbase[t] = c != 0 ? atomicAdd(&supcur[t], c) : 0;
+            if (t == 0) total = tot;
+            if (ch + 1 < CHUNKS) cnt[t] = 0;
         }
-        if (t == 0) total = tot;
-    }
-    __syncthreads();
+        __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (sup[r] >= 0) stage[lstart[sup[r]] + slot[r]] = rr[r];
-    __syncthreads();
-    const int n = total;
-    for (int j = t; j < n; j += 256) {
-        const PairRecord rec = stage[j];
-        const int sp = (rec.row >> shift) / kSupBuckets;
-        mid[gbase[sp] + (j - lstart[sp])] = rec;
+        for (int r = 0; r < R; ++r)
+            if (sup[ch * R + r] >= 0) stage[lstart[sup[ch * R + r]] + slot[r]] = rr[ch * R + r];
+        __syncthreads();
+        const int n = total;
+        for (int j = t; j < n; j += THREADS) {
+            const PairRecord rec = stage[j];
+            const int sp = (rec.row >> shift) / kSupBuckets;
+            mid[gbase[sp] + (j - lstart[sp])] = rec;
+        }
+        if (ch + 1 < CHUNKS) __syncthreads();
     }
 }
 
-template <int D>
-hipError_t launch_coef_split(int32_t nh, hipStream_t stream, const uint16_t* q, const uint16_t* kk,
+template <int D, int DV>
+hipError_t launch_coef_split(int64_t nh, hipStream_t stream, const uint16_t* q, const uint16_t* kk,
                              const uint16_t* v, const uint16_t* g, const int32_t* idx, const float* lse,
                              const int32_t* perm, int32_t N, int32_t H, int32_t k, float scale, float* dQ,
                              uint16_t* qg, int32_t shift, int32_t* supcur, PairRecord* mid, const uint8_t* keep,
                              float keep_scale) {
     const int ns = (k + 15) / 16;
-#define KMIP_COEF_SPLIT(NSV)                                                                           \
-    hipLaunchKernelGGL((coef_split_kernel<D, NSV>), dim3((unsigned)((nh + 128 / NSV - 1) / (128 / NSV))),   \
-                       dim3(256), 0, stream, q, kk, v, g, idx, lse, perm, N, H, k, scale, dQ, qg, shift, supcur, mid, \
-                       keep, keep_scale)
-    if (ns <= 1)
-        KMIP_COEF_SPLIT(1);
-    else if (ns <= 2)
-        KMIP_COEF_SPLIT(2);
-    else if (ns <= 4)
-        KMIP_COEF_SPLIT(4);
-    else
-        KMIP_COEF_SPLIT(8);
+#define KMIP_COEF_SPLIT(NSV)                                                                                    \
+    {                                                                                                           \
+        constexpr int per = split_threads(NSV) / 16 * (NSV <= 8 ? 8 / NSV : 1);                                 \
+        hipLaunchKernelGGL((coef_split_kernel<D, DV, NSV>), dim3((unsigned)((nh + per - 1) / per)),              \
+                           dim3(split_threads(NSV)), 0, stream, q, kk, v, g, idx, lse, perm, N, H, k, scale, dQ, \
+                           qg, shift, supcur, mid, keep, keep_scale);                                            \
+        return hipGetLastError();                                                                               \
+    }
+    if (ns <= 1) KMIP_COEF_SPLIT(1)
+    if (ns <= 2) KMIP_COEF_SPLIT(2)
+    if (ns <= 4) KMIP_COEF_SPLIT(4)
+    if (ns <= 8) KMIP_COEF_SPLIT(8)
+    if constexpr (D <= 64) {
+        if (ns <= 16) KMIP_COEF_SPLIT(16)
+        KMIP_COEF_SPLIT(32)
+    }
 #undef KMIP_COEF_SPLIT
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 constexpr int kPiece = 4096;   // records per reduction workgroup (sorted in 48 KB of LDS)
@@ -954,10 +965,10 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
 // threads:
 //   1. counting sort of the piece's records by key row into LDS (claim_slot:
 //      a key most pairs share costs about one LDS atomic per wave);
-//   2. LG = D/4 lanes take a contiguous span of the sorted records.  A record's
-//      query row of the interleaved head-major copy (q then dO, 4d bytes) is
-//      one 16-byte load per lane; the first half of the lanes add a*q to dK,
-//      the second p*dO to dV, eight records' rows in flight.  A key row whose
+//   2. LG lanes take a contiguous span of the sorted records.  A record's
+//      query row of the interleaved head-major copy (q then dO) is one 16-byte
+//      load per lane; the lanes of q add a*q to dK, those of dO p*dO to dV,
+//      four records' rows in flight.  A key row whose
 //      records all lie in the span is stored (added with atomics where the
 //      bucket has several pieces); the row a span starts in the middle of and
 //      the one it ends in go to LDS;
@@ -973,20 +984,23 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
 // an LDS float add took about four clocks a lane.)
 constexpr int kSumThreads = 512;
 
-template <int D>
+constexpr int pow2_at_least(int x) { return x <= 1 ? 1 : 2 * pow2_at_least((x + 1) / 2); }
+
+template <int D, int DV>
 __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t* __restrict__ QG,
                                                                  const BucketRecord* __restrict__ rec,
                                                                  const int32_t* __restrict__ sstart,
                                                                  const int32_t* __restrict__ pstart, int32_t nbk,
                                                                  int32_t shift, float* __restrict__ dK,
                                                                  float* __restrict__ dV) {
-    constexpr int LG = D / 4;                  // lanes per record
+    constexpr int RW = D + DV;                 // elements of a query row: q, then dO
+    constexpr int LG = pow2_at_least(RW / 8);  // lanes per record (those past the row idle)
     constexpr int GR = kSumThreads / LG;       // lane groups
     constexpr int B = 4;                       // records of a group in flight
     constexpr int PER = kPiece / kSumThreads;  // records per thread in the sort
     constexpr int SEG = 16;                    // partial rows summed by one thread
-    static_assert(2 * GR * D * 2 * sizeof(float) <= kPiece * sizeof(BucketRecord), "partial rows fit the records' area");
-    static_assert(kSumThreads / (2 * D) * SEG == 2 * GR, "every partial row has its threads");
+    static_assert(2 * GR * RW * sizeof(float) <= kPiece * sizeof(BucketRecord), "partial rows fit the records' area");
+    static_assert(kSumThreads / (8 * LG) * SEG == 2 * GR, "every partial row has its threads");
     static_assert(kMaxBucketRows <= kSumThreads, "one counter a thread in the scan");
     __shared__ BucketRecord srt[kPiece];
     __shared__ int32_t base[kMaxBucketRows + 1];
@@ -1040,9 +1054,10 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
 
     // 2. spans of the sorted records
     const int c = t & (LG - 1), grp = t / LG;
-    const bool isq = c < LG / 2;
-    const uint16_t* const col = QG + 8 * c;
-    float* const dst = (isq ? dK : dV) + ((size_t)lo << shift) * D + 8 * (c & (LG / 2 - 1));
+    const bool isq = c < D / 8, used = c < RW / 8;
+    const uint16_t* const col = QG + (used ? 8 * c : 0);
+    const size_t width = isq ? D : DV;
+    float* const dst = isq ? dK + ((size_t)lo << shift) * D + 8 * c : dV + ((size_t)lo << shift) * DV + (8 * c - D);
     const int span = ((n + GR - 1) / GR) | 1;   // odd: the groups' 12-byte records start in different banks
     const int p0 = min(n, grp * span), p1 = min(n, p0 + span);
     int32_t cur = -1, row0 = -1, row1 = -1;   // current row; rows of the span's partial sums
@@ -1059,13 +1074,14 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
             } else if (f1 > p1) {
                 row1 = cur;   // the last row: its sums stay in acc
                 return;
+            } else if (!used) {
             } else if (alone) {
-                float4* d4 = reinterpret_cast<float4*>(dst + (size_t)cur * D);
+                float4* d4 = reinterpret_cast<float4*>(dst + cur * width);
                 d4[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
                 d4[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
             } else {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) atomicAdd(dst + (size_t)cur * D + e, acc[e]);
+                for (int e = 0; e < 8; ++e) atomicAdd(dst + cur * width + e, acc[e]);
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
@@ -1077,7 +1093,7 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             rr[b] = srt[min(i0 + b, p1 - 1)];
-            x[b] = *reinterpret_cast<const uint4*>(col + (size_t)(rr[b].packed & ((1u << kQRowBits) - 1u)) * (2 * D));
+            x[b] = *reinterpret_cast<const uint4*>(col + (size_t)(rr[b].packed & ((1u << kQRowBits) - 1u)) * RW);
         }
 #pragma unroll
         for (int b = 0; b < B; ++b) {
@@ -1094,12 +1110,12 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
     }
     flush();
     __syncthreads();   // every record has been read: partial rows take their place
-    float* const part = reinterpret_cast<float*>(srt);   // [2 GR][2 D]
+    float* const part = reinterpret_cast<float*>(srt);   // [2 GR][RW]
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const int32_t row = side == 0 ? row0 : row1;
-        if (row >= 0) {
-            float* d8 = part + (size_t)(2 * grp + side) * (2 * D) + 8 * c;
+        if (row >= 0 && used) {
+            float* d8 = part + (size_t)(2 * grp + side) * RW + 8 * c;
 #pragma unroll
             for (int e = 0; e < 8; ++e) d8[e] = side == 0 ? acc0[e] : acc[e];
             if (c == 0) prow[2 * grp + side] = row;
@@ -1108,46 +1124,50 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
     __syncthreads();
 
     // 3. partial rows, an element a thread
-    const int el = t % (2 * D), sg = t / (2 * D);
-    float* const out = (el < D ? dK : dV) + ((size_t)lo << shift) * D + (el < D ? el : el - D);
+    const int el = t % (8 * LG), sg = t / (8 * LG);
+    if (el >= RW) return;
+    const size_t ew = el < D ? D : DV;
+    float* const out = el < D ? dK + ((size_t)lo << shift) * D + el : dV + ((size_t)lo << shift) * DV + (el - D);
     int32_t at = -1;
     float v = 0.0f;
     for (int i = sg * SEG; i < sg * SEG + SEG; ++i) {
         const int32_t row = prow[i];
         if (row < 0) continue;
         if (row != at) {
-            if (at >= 0) atomicAdd(out + (size_t)at * D, v);
+            if (at >= 0) atomicAdd(out + at * ew, v);
             at = row;
             v = 0.0f;
         }
-        v += part[(size_t)i * (2 * D) + el];
+        v += part[(size_t)i * RW + el];
     }
-    if (at >= 0) atomicAdd(out + (size_t)at * D, v);
+    if (at >= 0) atomicAdd(out + at * ew, v);
 }
 
 }  // namespace
 
-bool bwd_bucket_supported(int32_t N, int32_t H, int32_t d, int32_t k) {
-    // the coefficient pass is built for d <= 64 and at most 8 slots a lane
-    if (d > 64 || k > 128) return false;
+bool bwd_bucket_rows(int32_t N, int32_t H, int32_t d) {
     const int64_t nh = (int64_t)N * H;
     const int sh = bucket_shift(nh, d);
     return ((nh + (1 << sh) - 1) >> sh) <= kMaxBuckets;
 }
 
-size_t bwd_bucket_workspace_bytes(int32_t N, int32_t H, int32_t d, int32_t k) {
+bool bwd_bucket_supported(int32_t N, int32_t H, int32_t d, int32_t k) {
+    return d <= 64 && k <= 128 && bwd_bucket_rows(N, H, d);
+}
+
+size_t bwd_bucket_workspace_bytes(int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t nh = (size_t)N * H, pairs = nh * k;
     const size_t nbk = (nh + ((size_t)1 << bucket_shift((int64_t)nh, d)) - 1) >> bucket_shift((int64_t)nh, d);
     const size_t nb = (nbk + 1 + kScanBlock - 1) / kScanBlock;
     return al(pairs * sizeof(BucketRecord)) + 3 * al((nbk + 1) * sizeof(int32_t)) +
-           al((nb + 1) * sizeof(int32_t)) + al(nh * 2 * d * sizeof(uint16_t)) + al(pairs * sizeof(PairRecord)) +
+           al((nb + 1) * sizeof(int32_t)) + al(nh * (d + dv) * sizeof(uint16_t)) + al(pairs * sizeof(PairRecord)) +
            3 * al((kMaxSup + 1) * sizeof(int32_t)) + al(group_workspace_bytes(N, H, d));
 }
 
 hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const void* dO,
                              const int32_t* idx, const float* lse, const uint8_t* keep, float keep_scale,
-                             int32_t N, int32_t H, int32_t d, int32_t k, float scale, float* dQ, float* dK,
+                             int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k, float scale, float* dQ, float* dK,
                              float* dV, void* ws, hipStream_t stream) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const int64_t nh = (int64_t)N * H;
@@ -1169,7 +1189,7 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     p += al(((size_t)nbk + 1) * sizeof(int32_t));
     p += al(((size_t)nb + 1) * sizeof(int32_t));
     uint16_t* qg = reinterpret_cast<uint16_t*>(p);   // q and dO interleaved, row h N + p for query perm[h][p]
-    p += al((size_t)nh * 2 * d * sizeof(uint16_t));
+    p += al((size_t)nh * (d + dv) * sizeof(uint16_t));
     PairRecord* mid = reinterpret_cast<PairRecord*>(p);   // records in super-bucket order (pass 1)
     p += al(pairs * sizeof(PairRecord));
     int32_t* supst = reinterpret_cast<int32_t*>(p);
@@ -1190,13 +1210,13 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     // (measured: 2^24 pairs and more; below, the plain order is as fast or
     // faster, 14% at 1.7M pairs in a batch of small graphs).
     QueryGroups groups{};
-    if ((int64_t)pairs >= (int64_t(1) << 24) &&
+    if ((int64_t)pairs >= (int64_t(1) << 24) && d <= 64 &&
         (e = launch_group_queries(Q, N, H, d, gws, &groups, stream)) != hipSuccess)
         return e;
-    const int64_t g4 = ((int64_t)nbk + 1 + 3) / 4, n4 = nh * d / 4;
-    const unsigned zblocks = (unsigned)std::min<int64_t>((g4 + 2 * n4 + 255) / 256, 256 * 32);
+    const int64_t g4 = ((int64_t)nbk + 1 + 3) / 4, n4 = nh * d / 4, m4 = nh * dv / 4;
+    const unsigned zblocks = (unsigned)std::min<int64_t>((g4 + n4 + m4 + 255) / 256, 256 * 32);
     hipLaunchKernelGGL(bkt_clear_kernel, dim3(zblocks), dim3(256), 0, stream, reinterpret_cast<int4*>(gcnt), g4,
-                       reinterpret_cast<float4*>(dK), n4, reinterpret_cast<float4*>(dV), n4);
+                       reinterpret_cast<float4*>(dK), n4, reinterpret_cast<float4*>(dV), m4);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // pairs per counting workgroup: about 1024 workgroups, 2048 .. 65536 pairs
     // each (1.7M pairs in 209 workgroups of 8192 took 32 us)
@@ -1211,28 +1231,35 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
                        supcur, pstart2);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // coefficients, dQ and the interleaved copy, fused with placement pass 1
-    if (d == 16)
-        e = launch_coef_split<16>((int32_t)nh, stream, q, kk, v, g, idx, lse, groups.perm, N, H, k, scale, dQ, qg, shift, supcur,
-                                  mid, keep, keep_scale);
-    else if (d == 32)
-        e = launch_coef_split<32>((int32_t)nh, stream, q, kk, v, g, idx, lse, groups.perm, N, H, k, scale, dQ, qg, shift, supcur,
-                                  mid, keep, keep_scale);
-    else
-        e = launch_coef_split<64>((int32_t)nh, stream, q, kk, v, g, idx, lse, groups.perm, N, H, k, scale, dQ, qg, shift, supcur,
-                                  mid, keep, keep_scale);
+    e = hipErrorInvalidValue;
+#define KMIP_SPLIT(DD, DVV)                                                                                   \
+    if (d == DD && dv == DVV)                                                                                  \
+        e = launch_coef_split<DD, DVV>(nh, stream, q, kk, v, g, idx, lse, groups.perm, N, H, k, scale, dQ, qg, shift, \
+                                       supcur, mid, keep, keep_scale);
+#define KMIP_SPLIT_D(DD) KMIP_SPLIT(DD, 16) KMIP_SPLIT(DD, 32) KMIP_SPLIT(DD, 64) KMIP_SPLIT(DD, 128)
+    KMIP_SPLIT_D(16)
+    KMIP_SPLIT_D(32)
+    KMIP_SPLIT_D(64)
+    KMIP_SPLIT_D(128)
+#undef KMIP_SPLIT_D
+#undef KMIP_SPLIT
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(bkt_split2_kernel, dim3((unsigned)(nsup + (pairs + kSplitChunk - 1) / kSplitChunk)), dim3(256),
                        0, stream, mid, supst, pstart2, nsup, shift, gcnt, rec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // at most one piece per bucket plus one per kPiece pairs; the rest exit
     const unsigned rblocks = (unsigned)(nbk + (pairs + kPiece - 1) / kPiece);
-#define KMIP_BKT_REDUCE(DD)                                                                                    \
-    if (d == DD)                                                                                               \
-        hipLaunchKernelGGL(bkt_reduce_kernel<DD>, dim3(rblocks), dim3(kSumThreads), 0, stream, qg, rec, sstart, \
+#define KMIP_BKT_REDUCE(DD, DVV)                                                                               \
+    if (d == DD && dv == DVV)                                                                                  \
+        hipLaunchKernelGGL((bkt_reduce_kernel<DD, DVV>), dim3(rblocks), dim3(kSumThreads), 0, stream, qg, rec, sstart, \
                            pstart, nbk, shift, dK, dV);
-    KMIP_BKT_REDUCE(16)
-    KMIP_BKT_REDUCE(32)
-    KMIP_BKT_REDUCE(64)
+#define KMIP_BKT_REDUCE_D(DD) \
+    KMIP_BKT_REDUCE(DD, 16) KMIP_BKT_REDUCE(DD, 32) KMIP_BKT_REDUCE(DD, 64) KMIP_BKT_REDUCE(DD, 128)
+    KMIP_BKT_REDUCE_D(16)
+    KMIP_BKT_REDUCE_D(32)
+    KMIP_BKT_REDUCE_D(64)
+    KMIP_BKT_REDUCE_D(128)
+#undef KMIP_BKT_REDUCE_D
 #undef KMIP_BKT_REDUCE
     return hipGetLastError();
 }

@@ -163,7 +163,7 @@ inline bool gather_by_head(int32_t N, int32_t H, int32_t d, int32_t dv, int32_t 
 }
 
 // The backward launchers take the query/key width d and the value width dv
-// (each in {16, 32, 64}); the bucketed one needs dv == d.
+// (each in {16, 32, 64, 128}).
 hipError_t launch_bwd_atomic(const void* Q, const void* K, const void* V, const void* dO,
                              const int32_t* idx, const float* lse, const uint8_t* keep, float keep_scale,
                              int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k, float scale, float* dQ,
@@ -184,14 +184,16 @@ hipError_t launch_bwd_csr(const void* Q, const void* K, const void* V, const voi
                           int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k, float scale, float* dQ,
                           float* dK, float* dV, void* ws, hipStream_t stream);
 
-// Backward with pairs bucketed by blocks of key rows and summed in LDS
-// (backward_csr.hip); supported for d <= 64 and k <= 128 while
-// N * H / (4096 / d) <= 8192.
+// Backward with pairs bucketed by blocks of key rows (backward_csr.hip), for
+// every width and k while the key rows fit its bucket table
+// (bwd_bucket_rows); KMIP_BWD_BUCKETED stands for it where dv == d <= 64 and
+// k <= 128 (bwd_bucket_supported).
+bool bwd_bucket_rows(int32_t N, int32_t H, int32_t d);
 bool bwd_bucket_supported(int32_t N, int32_t H, int32_t d, int32_t k);
-size_t bwd_bucket_workspace_bytes(int32_t N, int32_t H, int32_t d, int32_t k);
+size_t bwd_bucket_workspace_bytes(int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k);
 hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const void* dO,
                              const int32_t* idx, const float* lse, const uint8_t* keep, float keep_scale,
-                             int32_t N, int32_t H, int32_t d, int32_t k, float scale, float* dQ, float* dK,
+                             int32_t N, int32_t H, int32_t d, int32_t dv, int32_t k, float scale, float* dQ, float* dK,
                              float* dV, void* ws, hipStream_t stream);
 
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t stream);

@@ -29,6 +29,9 @@ CASES = [(70, 2, d, dv, k) for d, dv, k in (
     (16, 16, 1), (16, 16, 17), (16, 32, 16), (16, 64, 33), (16, 128, 128), (32, 16, 15), (32, 32, 16), (32, 32, 65),
     (32, 64, 32), (32, 128, 8), (64, 16, 129), (64, 32, 17), (64, 64, 1), (64, 64, 128), (64, 128, 31), (128, 16, 5),
     (128, 32, 128), (128, 64, 16), (128, 128, 33))]
+# more than 2^20 pairs at d = 128 and k > 128: the bucketed reduction's forms for
+# them (k up to 256 and 512: 8 and 4 teams a workgroup)
+CASES += [(3001, 3, 128, 128, 128), (2050, 2, 32, 32, 300), (2100, 4, 64, 64, 129), (4099, 2, 16, 16, 512)]
 # by head (wide rows, large k; a partly filled last workgroup per head)
 CASES += [(1025, 3, 32, 32, 257), (1030, 2, 16, 16, 512), (1024, 3, 128, 128, 16), (1025, 3, 64, 64, 20)]
 
@@ -39,12 +42,18 @@ def test_given_sets(case):
     rng = np.random.default_rng(d + dv + k)
     w = workloads.iid(N, H, d, min(k, N), seed=N + d + dv + k, dv=dv)
     # distinct keys per row where there are enough, random holes, a row without any
-    idx = np.argsort(rng.random((N, H, N), dtype=np.float32), axis=2)[:, :, :k].astype(np.int32)
-    idx = np.concatenate([idx, np.full((N, H, k - idx.shape[2]), -1, np.int32)], axis=2)
+    if N > 2000:   # (a stride coprime to a prime modulus above N keeps a row's keys distinct)
+        step = rng.integers(1, 4799, (N, H, 1))
+        idx = ((rng.integers(0, 4799, (N, H, 1)) + step * np.arange(k)) % 4799).astype(np.int32)
+        idx[idx >= N] = -1
+    else:
+        idx = np.argsort(rng.random((N, H, N), dtype=np.float32), axis=2)[:, :, :k].astype(np.int32)
+        idx = np.concatenate([idx, np.full((N, H, k - idx.shape[2]), -1, np.int32)], axis=2)
     holes = rng.random(idx.shape) < 0.1
     idx[0] = -1
     gpu_idx = np.where(holes, rng.choice(np.array([-1, -7, N, 2**31 - 1], np.int32), idx.shape), idx)
     ref_idx = np.where(holes, -1, idx)
+    assert ((np.sort(ref_idx, 2)[:, :, 1:] != np.sort(ref_idx, 2)[:, :, :-1]) | (np.sort(ref_idx, 2)[:, :, 1:] < 0)).all()
     rate = 0.25 if k % 2 else 0.0
     keep = (rng.random(idx.shape) >= rate).astype(np.uint8) if rate else None
     kw = {} if keep is None else dict(keep=torch.from_numpy(keep).to(DEV), drop_rate=rate)
@@ -58,8 +67,26 @@ def test_given_sets(case):
     allclose_report("out", out.cpu().numpy().reshape(-1, dv), ro)
     allclose_report("lse", lse.cpu().numpy().reshape(-1), rl)
     grads = oracle.backward(Qd, Kd, Vd, Gd, ref_idx, w.scale, **okw)
-    variants = [_lib.BWD_SEGMENTED] + ([_lib.BWD_BUCKETED] if d == dv <= 64 and k <= 128 else [])
+    variants = [_lib.BWD_AUTO, _lib.BWD_SEGMENTED] + ([_lib.BWD_BUCKETED] if d == dv <= 64 and k <= 128 else [])
     for variant in variants:
         got = kmip.bwd(q, kk, v, g, gi, lse, w.scale, variant=variant, **kw)
         for name, a, r in zip(("dQ", "dK", "dV"), got, grads):
             allclose_report(f"{name} v{variant}", a.cpu().numpy(), r)
+
+
+def test_key_sort_workspace_still_taken():
+    # a workspace that holds only the key sort's arrays gets the key sort
+    N, H, d, dv, k = 600, 2, 32, 64, 16
+    w = workloads.iid(N, H, d, k, seed=5, dv=dv)
+    q, kk, v, g = _dev(w.q), _dev(w.kk), _dev(w.v), _dev(w.dout)
+    small = kmip.bwd_workspace_size(N, H, d, k, _lib.BWD_SEGMENTED, dv=dv)
+    assert small < kmip.bwd_workspace_size(N, H, d, k, _lib.BWD_AUTO, dv=dv)
+    out, idx, lse = kmip.fwd(q, kk, v, k, w.scale)
+    buf = torch.empty(small, dtype=torch.uint8, device=DEV)
+    got = [torch.empty(N, H, x, device=DEV) for x in (d, d, dv)]
+    _lib.check(_lib.load().kmip_bwd_ex(q.data_ptr(), kk.data_ptr(), v.data_ptr(), g.data_ptr(), idx.data_ptr(), lse.data_ptr(),
+                                       None, 0.0, N, H, d, dv, k, w.scale, *(t.data_ptr() for t in got), _lib.BWD_AUTO,
+                                       buf.data_ptr(), small, torch.cuda.current_stream().cuda_stream))
+    want = kmip.bwd(q, kk, v, g, idx, lse, w.scale)
+    for name, a, b in zip(("dQ", "dK", "dV"), got, want):
+        allclose_report(name, a.cpu().numpy(), b.cpu().numpy(), atol=1e-5, rtol=1e-4)   # 32-bit sums in another order
