@@ -14,6 +14,7 @@ with the index slots (nonzero keeps a slot's weight, scaled by
 from __future__ import annotations
 
 import ctypes
+import functools
 from typing import Optional, Sequence
 
 import numpy as np
@@ -322,24 +323,33 @@ def attention(q, k_, v, kk: int, scale: float, graph_offsets=None, variant: int 
     keep / drop_rate: attention dropout draws uint8 [N, H, kk] and rate,
     used by the forward and again by the backward.
     """
+    return _attention_function().apply(q, k_, v, kk, scale, graph_offsets, variant, workspace, keep, drop_rate)
+
+
+@functools.lru_cache(maxsize=None)
+def _attention_function():
+    """The autograd function of ``attention`` (made once: building a Function
+    class takes the host longer than launching the kernels)."""
     torch = _torch()
 
     class _Attention(torch.autograd.Function):
         @staticmethod
-        def forward(ctx, q_, k2, v_):
-            out, idx, lse = fwd(q_, k2, v_, kk, scale, graph_offsets=graph_offsets, workspace=workspace,
+        def forward(ctx, q, k_, v, kk, scale, graph_offsets, variant, workspace, keep, drop_rate):
+            out, idx, lse = fwd(q, k_, v, kk, scale, graph_offsets=graph_offsets, workspace=workspace,
                                 keep=keep, drop_rate=drop_rate)
-            ctx.save_for_backward(q_, k2, v_, idx, lse)
+            ctx.save_for_backward(q, k_, v, idx, lse)
+            ctx.args = scale, variant, workspace, keep, drop_rate
             return out
 
         @staticmethod
         def backward(ctx, dout):
-            q_, k2, v_, idx, lse = ctx.saved_tensors
-            dq, dk, dv = bwd(q_, k2, v_, dout.to(torch.bfloat16).contiguous(), idx, lse, scale,
+            q, k_, v, idx, lse = ctx.saved_tensors
+            scale, variant, workspace, keep, drop_rate = ctx.args
+            dq, dk, dv = bwd(q, k_, v, dout.to(torch.bfloat16).contiguous(), idx, lse, scale,
                              variant=variant, workspace=workspace, keep=keep, drop_rate=drop_rate)
-            return dq.to(q_.dtype), dk.to(k2.dtype), dv.to(v_.dtype)
+            return (dq.to(q.dtype), dk.to(k_.dtype), dv.to(v.dtype), *[None] * 7)
 
-    return _Attention.apply(q, k_, v)
+    return _Attention
 
 
 from .layer import KMIPAttention, linear_k_schedule  # noqa: E402
