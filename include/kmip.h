@@ -34,11 +34,10 @@
  *    for d <= 64 and 1 <= k <= KMIP_MAX_K_WIDE (128) for d = 128; H >= 1;
  *    0 <= N < 2^31 and N * H * max(d, k) < 2^31.  (The bound on N * H * k
  *    is also what keeps node ids below 2^(32 - ceil(log2 k)), the room the
- *    select kernel's on-chip trees leave for an index.)  The fastest paths
- *    are those of d <= 64 and k <= 128: the direction grouping and the key
- *    order with bounds that let the select kernel skip key blocks are built
- *    for d <= 64 only, and a larger k gives the kernel larger trees in LDS
- *    (fewer resident waves).
+ *    streaming select kernel's on-chip trees leave for an index.)  Small and
+ *    medium graphs, d = 128 and k > 128 are selected in two dense passes over
+ *    the keys; large graphs of d <= 64 are grouped by direction and their keys
+ *    ordered with bounds that let the streaming kernel skip key blocks.
  *  - stream: a hipStream_t (NULL = the default stream).  Every call is
  *    asynchronous on `stream`; the caller synchronises.
  *  - Ownership: the caller allocates every buffer (inputs, outputs and the
@@ -188,7 +187,7 @@ kmip_status_t kmip_fwd_ex(const void* Q, const void* K, const void* V, const int
  * select_stop as kmip_topk_with_events does (around the score+select
  * kernel alone), attend_start right before the aggregate.  Each may be NULL
  * to record nothing.  In every kmip_fwd* call on one graph that the library
- * groups by direction (at least 8192 nodes, d <= 64) the aggregate takes
+ * groups by direction (large graphs, d <= 64) the aggregate takes
  * the query-heads in that grouped order, so that the queries of a
  * workgroup share their keys' rows; results do not depend on the order.
  */
@@ -268,8 +267,8 @@ kmip_status_t kmip_bwd(const void* Q, const void* K, const void* V, const void* 
  * KMIP_BWD_BUCKETED needs dv == d (else KMIP_ERR_UNSUPPORTED and workspace
  * size 0): its interleaved copy of q_i and dOut_i assumes equal widths;
  * KMIP_BWD_AUTO then runs the bucketed reduction in its form for unequal
- * widths, while N*H <= 8192*512, or KMIP_BWD_SEGMENTED where the workspace
- * passed holds only that one's arrays.  kmip_bwd and
+ * widths (more than 2^16 pairs, N*H <= 8192*512), or KMIP_BWD_SEGMENTED, also
+ * where the workspace passed holds only that one's arrays.  kmip_bwd and
  * kmip_bwd_workspace_size are the case dv = d, keep = NULL.
  */
 size_t kmip_bwd_ex_workspace_size(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k, int32_t variant);

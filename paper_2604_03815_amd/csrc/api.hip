@@ -189,7 +189,11 @@ enum SelectPath { kPathResident = 0, kPathDense = 1, kPathStream = 2 };
 // streaming kernel, whose waves keep to the same tiles, is as fast.  Above
 // k = 128 the streaming kernel's trees leave room for one or two waves per
 // CU (k = 256, 200k nodes, 2 heads, d = 16: 27 against 14 ms).
-SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
+// A dense launch has a workgroup per 32 queries and head (N, G: nodes and
+// graphs of the whole call), kept below 2^31 threads: more (many heads of a
+// few nodes) go to the persistent grid of the streaming kernel.
+SelectPath select_path(int64_t n, int64_t N, int32_t G, int32_t H, int32_t d, int32_t k) {
+    if ((N / 32 + G) * H > (int64_t(1) << (k > KMIP_MAX_K_WIDE ? 20 : 22))) return kPathStream;
     if (n <= kmip::kResidentGraph && k <= KMIP_MAX_K_WIDE) return kPathResident;
     int64_t most = 65536;
     if (k > KMIP_MAX_K_WIDE)
@@ -211,7 +215,7 @@ SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
 // whichever path takes it.)
 bool sized_for_grouping(int64_t N, int32_t G, int32_t d) { return G == 1 && N >= 8192 && d <= 64; }
 bool use_grouping(int64_t N, int32_t G, int32_t H, int32_t d, int32_t k) {
-    return sized_for_grouping(N, G, d) && select_path(N, G, H, d, k) == kPathStream;
+    return sized_for_grouping(N, G, d) && select_path(N, N, G, H, d, k) == kPathStream;
 }
 
 // Queries per dense task: 64 share each key tile's load once the scan outweighs
@@ -344,7 +348,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
         largest = 0;
         for (int32_t g = 0; g < G; ++g) {
             const int64_t n = graph_offsets[g + 1] - graph_offsets[g];
-            if (select_path(n, G, H, d, k) == kPathDense) largest = std::max(largest, n);
+            if (select_path(n, N, G, H, d, k) == kPathDense) largest = std::max(largest, n);
         }
     }
     const int32_t run = dense_run(largest, d, k);
@@ -362,7 +366,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
             const size_t first = tasks.size();
             for (int32_t g = 0; g < G; ++g) {
                 const int32_t lo = graph_offsets[g], hi = graph_offsets[g + 1];
-                if (select_path(hi - lo, G, H, d, k) != path) continue;
+                if (select_path(hi - lo, N, G, H, d, k) != path) continue;
                 const int32_t step = step_of(path);
                 for (int32_t q0 = lo; q0 < hi; q0 += step)
                     tasks.push_back(kmip::Task{q0, std::min(step, hi - q0), lo, hi});
@@ -377,7 +381,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
         if (e != hipSuccess) return hip_fail(e, "work list upload");
         dtasks = reinterpret_cast<const kmip::Task*>(dst);
     } else {
-        const SelectPath path = select_path(N, G, H, d, k);
+        const SelectPath path = select_path(N, N, G, H, d, k);
         const int32_t step = step_of(path);
         count[path] = (int32_t)((N + step - 1) / step);
     }
@@ -546,16 +550,16 @@ static int32_t default_bwd_variant(int64_t N, int32_t H, int32_t d, int32_t dv, 
 // Whether KMIP_BWD_AUTO runs the bucketed reduction where it would pick the
 // key sort (unequal widths, d = 128, k > 128): its workspace is larger
 // (28 against 24 bytes a pair, and the interleaved query rows), and a caller
-// whose workspace holds only the key sort's gets that.  With equal widths and
-// up to 2^20 pairs the key sort, and its smaller workspace, stay (there its
-// passes over the index rows, uncoalesced for a large k, cost little).  Whole
+// whose workspace holds only the key sort's gets that.  Up to 2^20 pairs with
+// equal widths, and 2^16 with unequal ones, the key sort and its smaller
+// workspace stay (its passes over the index rows cost little there).  Whole
 // backward, key sort against buckets (us): 1,500 nodes, 3 heads, d = 32, d_V =
 // 64, k = 16 149 and 76; 60,000 nodes of the same 359 and 305; 10,000 nodes, 4
 // heads, d = 128, k = 32 404 and 262; 3,000 nodes, 2 heads, d = 32, k = 256
 // 1066 and 157; 30,000 nodes, 2 heads, d = 128, k = 100 1512 and 1391.
 static bool wide_buckets(int64_t N, int32_t H, int32_t d, int32_t dv, int32_t k) {
     const int64_t pairs = N * (int64_t)H * k;
-    return default_bwd_variant(N, H, d, dv, k) == KMIP_BWD_SEGMENTED && (dv != d || pairs > (1 << 20)) &&
+    return default_bwd_variant(N, H, d, dv, k) == KMIP_BWD_SEGMENTED && pairs > (dv == d ? 1 << 20 : 1 << 16) &&
            kmip::bwd_bucket_rows((int32_t)N, H, d);
 }
 

@@ -29,9 +29,9 @@ CASES = [(70, 2, d, dv, k) for d, dv, k in (
     (16, 16, 1), (16, 16, 17), (16, 32, 16), (16, 64, 33), (16, 128, 128), (32, 16, 15), (32, 32, 16), (32, 32, 65),
     (32, 64, 32), (32, 128, 8), (64, 16, 129), (64, 32, 17), (64, 64, 1), (64, 64, 128), (64, 128, 31), (128, 16, 5),
     (128, 32, 128), (128, 64, 16), (128, 128, 33))]
-# more than 2^20 pairs at d = 128 and k > 128: the bucketed reduction's forms for
-# them (k up to 256 and 512: 8 and 4 teams a workgroup)
-CASES += [(3001, 3, 128, 128, 128), (2050, 2, 32, 32, 300), (2100, 4, 64, 64, 129), (4099, 2, 16, 16, 512)]
+# more than 2^20 pairs at d = 128 and k > 128, 2^16 at unequal widths: the bucketed
+# reduction's forms for them (k up to 256 and 512: 8 and 4 teams a workgroup)
+CASES += [(3001, 3, 128, 128, 128), (2100, 2, 32, 64, 16), (2051, 3, 64, 16, 20), (2060, 1, 16, 128, 40), (2050, 2, 32, 32, 300), (2100, 4, 64, 64, 129), (4099, 2, 16, 16, 512)]
 # by head (wide rows, large k; a partly filled last workgroup per head)
 CASES += [(1025, 3, 32, 32, 257), (1030, 2, 16, 16, 512), (1024, 3, 128, 128, 16), (1025, 3, 64, 64, 20)]
 
@@ -76,7 +76,7 @@ def test_given_sets(case):
 
 def test_key_sort_workspace_still_taken():
     # a workspace that holds only the key sort's arrays gets the key sort
-    N, H, d, dv, k = 600, 2, 32, 64, 16
+    N, H, d, dv, k = 3000, 2, 32, 64, 16
     w = workloads.iid(N, H, d, k, seed=5, dv=dv)
     q, kk, v, g = _dev(w.q), _dev(w.kk), _dev(w.v), _dev(w.dout)
     small = kmip.bwd_workspace_size(N, H, d, k, _lib.BWD_SEGMENTED, dv=dv)
