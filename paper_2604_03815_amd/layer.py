@@ -44,28 +44,6 @@ def linear_k_schedule(k_start: int, k_end: int, steps: int) -> Callable[[int], i
     return k_at
 
 
-def _matmul_rows(x, weights):
-    """[x @ w for w in weights].  In training the rows are cut into slices of
-    256 or more, in one batched product with the weights side by side, shared
-    by the slices: autograd then forms the weight gradients x^T g (few outputs,
-    one long sum over the rows, which a plain product runs on a few
-    workgroups) as one product per slice and their sum, and the gradient of x
-    as one product.  A layer of 3 heads on 64 graphs (17k nodes): the four weight
-    gradients took 376 of the step's 860 us; the step 831 -> 587 us."""
-    N = x.shape[0]
-    most = min(64, N // 256)
-    if most < 4 or not (torch.is_grad_enabled() and any(w.requires_grad for w in weights)):
-        return [x @ w for w in weights]
-    # slices of equal length, padded only where no count from 16 divides N
-    S = next((c for c in range(most, min(most, 16) - 1, -1) if N % c == 0), most)
-    n = -(-N // S)
-    if S * n != N:
-        x = torch.nn.functional.pad(x, (0, 0, 0, S * n - N))
-    w = torch.cat([w.expand(S, *w.shape) for w in weights], 2) if len(weights) > 1 else weights[0].expand(S, -1, -1)
-    y = torch.bmm(x.reshape(S, n, x.shape[1]), w).view(S * n, -1)
-    return (y if S * n == N else y[:N]).split([w.shape[1] for w in weights], 1)
-
-
 class KMIPAttention(torch.nn.Module):
     """One layer of multi-head k-MIP self-attention (Eq. 1-2, Algorithm 1).
 
@@ -105,8 +83,10 @@ class KMIPAttention(torch.nn.Module):
     def project(self, x):
         """Q, K, V [N, H, width] in bf16, the library's input type."""
         N = x.shape[0]
-        y = _matmul_rows(x, [self.w_q, self.w_k, self.w_v])
-        return tuple(t.to(torch.bfloat16).contiguous().view(N, self.heads, -1) for t in y)
+        q = (x @ self.w_q).to(torch.bfloat16).view(N, self.heads, self.d_k)
+        k = (x @ self.w_k).to(torch.bfloat16).view(N, self.heads, self.d_k)
+        v = (x @ self.w_v).to(torch.bfloat16).view(N, self.heads, self.d_v)
+        return q, k, v
 
     def forward(self, x, graph_offsets=None, keep=None):
         """keep: optional uint8 [N, H, k] dropout keep mask (1 keeps a kept
@@ -123,4 +103,4 @@ class KMIPAttention(torch.nn.Module):
             keep = (torch.rand(q.shape[0], self.heads, kk, device=q.device) >= rate).to(torch.uint8)
         o = attention(q, k, v, kk, self.scale, graph_offsets=graph_offsets, variant=self.variant,
                       keep=keep if rate > 0.0 else None, drop_rate=rate)
-        return _matmul_rows(o.reshape(x.shape[0], self.heads * self.d_v), [self.w_o])[0]
+        return o.reshape(x.shape[0], self.heads * self.d_v) @ self.w_o
