@@ -349,8 +349,9 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         }
     };
 
-    // Whether some list counts more than x keys (the same answer for every
-    // wave, between two barriers).
+    // Whether some list counts more than x keys.  The same answer for every
+    // wave only if no wave changes a count between the barrier before the call
+    // and one after it: the waves branch to barriers on it.
     auto any_above = [&](int x) {
         return __builtin_amdgcn_ballot_w64(cnt[lane & (QN - 1)] > x) != 0ull;
     };
@@ -504,7 +505,9 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
             list_tile(acc, m, i, theta, bnd);
         }
         __syncthreads();
-        if (!any_above(CAP - 32)) continue;
+        const bool full = any_above(CAP - 32);
+        __syncthreads();   // every wave has read the counts: the next tile may list
+        if (!full) continue;
         const int m = active ? cnt[q] : 0;
         if (m > k) rank_all(m, false);
         __syncthreads();

@@ -72,3 +72,59 @@ def test_rows_equal_oracle(case):
     o_idx, _, _ = oracle.topk(oracle.from_bf16(qb), oracle.from_bf16(kb), k, offsets=offsets, **({} if sel is None else {"sel": sel}))
     got = idx.reshape(N * H, k)
     np.testing.assert_array_equal(got if sel is None else got[sel], o_idx)
+
+
+# Inputs whose lists overflow at every listing, so that the block walks the
+# tiles one at a time.  The good keys all lie in the first rows of every eighth
+# tile (sixteenth for k > 128): a handful of group maxima holds them, so the
+# threshold lies below all of them, and one wave lists them in rising order, so
+# a list of CAP keys raises the bound past CAP - k of them only.
+WALK = [
+    # (d, k, sizes, CAP); the walked graph is the largest
+    (16, 32, [28000], 128),            # 32 queries a block
+    (16, 32, [60000], 128),            # 64 queries a block
+    (128, 16, [24000], 128),           # sampled first pass
+    (32, 30, [33, 40000, 20], 128),    # a batch, the graph's first tile shared with another
+    (16, 128, [50000], 256),
+    (16, 256, [140000], 512),
+    (16, 512, [140000], 1024),         # 16 queries a block
+]
+
+
+@pytest.mark.parametrize("case", WALK, ids=lambda c: "d%d_k%d_N%d_G%d" % (c[0], c[1], sum(c[2]), len(c[2])))
+def test_tile_by_tile_walk(case):
+    d, k, sizes, cap = case
+    rng = np.random.default_rng(d + k)
+    N, big = sum(sizes), int(np.argmax(sizes))
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    lo, hi = int(offsets[big]), int(offsets[big + 1])
+    at = np.arange(N) - (lo & ~31)                 # row from the graph's first tile
+    period, rows = {128: (256, 4), 256: (256, 4), 512: (512, 4), 1024: (512, 8)}[cap]
+    good = (np.arange(N) >= lo) & (np.arange(N) < hi) & (at % period < rows)
+    M = int(good.sum())
+    assert M - 2 * (cap - k) > cap, "three listings overflow"
+    # scores 256 a + b of a query (256, 1, 0, ..): exact, the good ones rising
+    # and above all others
+    val = rng.integers(0, 25600, size=N)
+    val[good] = 51200 + np.arange(M)
+    kk = np.zeros((N, 1, d), np.float32)
+    kk[:, 0, 0], kk[:, 0, 1] = val // 256, val % 256
+    q = np.zeros((N, 1, d), np.float32)
+    q[:, 0, 0], q[:, 0, 1] = 256, 1
+    kind = rng.random(N)
+    q[kind < 0.2] *= -1                            # the lowest keys win
+    q[kind > 0.95] = 0                             # every key ties
+    qb, kb = workloads.bf16_round(q), workloads.bf16_round(kk)
+    print(f"[case] dense select walk N={N} d={d} k={k} sizes={sizes}", flush=True)
+    off = None if len(sizes) == 1 else offsets
+    idx = kmip.topk(_dev(qb), _dev(kb), k, graph_offsets=off)
+    torch.cuda.synchronize()
+    idx = idx.cpu().numpy()
+    check_structure(idx, off, N, 1, k)
+    got = idx.reshape(N, k)
+    up = (kind >= 0.2) & (kind <= 0.95) & (np.arange(N) >= lo) & (np.arange(N) < hi)
+    want = np.nonzero(good)[0][::-1][:k]
+    assert (got[up] == want).all(), "rows of the queries whose lists overflow"
+    sel = sample_rows(N, 1, 512, seed=5)
+    o_idx, _, _ = oracle.topk(oracle.from_bf16(qb), oracle.from_bf16(kb), k, offsets=off, sel=sel)
+    np.testing.assert_array_equal(got[sel], o_idx)
