@@ -30,12 +30,12 @@ def allclose_report(name, got, ref, atol=ATOL, rtol=RTOL):
     got = np.asarray(got, np.float64)
     ref = np.asarray(ref, np.float64)
     assert got.shape == ref.shape, (name, got.shape, ref.shape)
-    err = np.abs(got - ref)
-    bad = err > atol + rtol * np.abs(ref)
-    both_inf = np.isinf(got) & np.isinf(ref) & (np.sign(got) == np.sign(ref))
-    bad &= ~both_inf
+    # infinities must be the reference's own, and a NaN is outside any bound
+    inf = np.isinf(got) | np.isinf(ref)
+    err = np.abs(np.where(inf, 0.0, got) - np.where(inf, 0.0, ref))
+    bad = np.where(inf, got != ref, ~(err <= atol + rtol * np.abs(np.where(inf, 0.0, ref))))
     if bad.any():
-        i = np.argmax(np.where(bad, err, -1))
+        i = np.argmax(np.where(bad, np.where(inf | np.isnan(err), np.inf, err), -1))
         raise AssertionError(
             f"{name}: {int(bad.sum())} of {bad.size} elements outside "
             f"{atol}+{rtol}|r|; worst at flat {i}: got {got.flat[i]!r} ref {ref.flat[i]!r}")

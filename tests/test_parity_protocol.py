@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import workloads
-from parity import check_sets, check_sets_all, stratified_rows
+from parity import allclose_report, check_sets, check_sets_all, stratified_rows
 
 
 def _wl(seed=0):
@@ -79,3 +79,14 @@ def test_stratified_rows_cover_heads():
     sel = stratified_rows(Qd, 1000, seed=3)
     assert sel.size == 1000 and np.unique(sel).size == 1000
     assert np.all(np.bincount(sel % w.H, minlength=w.H) == 250)
+
+
+@pytest.mark.parametrize("got,ref", [(np.nan, 1.0), (np.nan, np.nan), (np.nan, -np.inf), (1.0, -np.inf), (np.inf, 1.0),
+                                     (np.inf, -np.inf), (1.1, 1.0)])
+def test_planted_value_fails(got, ref):
+    good = np.array([[0.5, -np.inf, 2.0], [np.inf, 0.0, -3.0]])
+    allclose_report("good", good, good)
+    a, b = good.copy(), good.copy()
+    a[1, 1], b[1, 1] = got, ref
+    with pytest.raises(AssertionError, match="1 of 6 elements"):
+        allclose_report("planted", a, b)
