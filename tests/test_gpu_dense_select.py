@@ -35,6 +35,11 @@ CASES = [
     (513, 3, 32, 16, None, "ints"),
     # lists that overflow: zero queries (every key ties), keys in order of score
     *[(3000, 1, 32, k, s, kind) for k, s in ((10, None), (128, [500, 2500]), (300, None)) for kind in ("zeros", "sorted")],
+    # few distinct keys: ties at every query's k-th best, listed again up to the bound
+    (9000, 2, 128, 32, None, "copies"),
+    (4000, 1, 64, 100, [1500, 2500], "copies"),
+    (31000, 1, 16, 16, None, "copies"),
+    (2600, 1, 32, 300, None, "copies"),
     # 64 queries a task; sampled first passes (every second, every third tile)
     (31000, 1, 16, 32, None, "ints"),
     (42000, 1, 16, 10, None, "ints"),
@@ -57,6 +62,8 @@ def test_rows_equal_oracle(case):
     kk = rng.integers(-1, 2, size=(N, H, d)).astype(np.float32)
     if kind == "zeros":
         q[rng.random(N) < 0.5] = 0
+    elif kind == "copies":
+        kk = kk[rng.integers(0, 50, N)]
     elif kind == "sorted":
         q[:] = 1
         kk[:] = 0
