@@ -8,15 +8,26 @@
 // B = 32 queries, fp32 accumulation over chunks of 16 dims), so they are the
 // same values.  Two passes over the keys, neither of which keeps a running
 // selection:
-//   1. every lane keeps the maxima of 4 T groups of the keys it scores (rows
-//      4 s .. 4 s + 3 of its 16 in every T-th of its tiles): 8 max3 a tile.
-//      The k'-th largest of a query's 8 T W group maxima (k' = min(k, n)) is
+//   1. every lane keeps the maxima of GT T groups of the keys it scores (16 /
+//      GT neighbouring rows of its 16 in every T-th of its tiles).
+//      The k'-th largest of a query's 2 GT T W group maxima (k' = min(k, n)) is
 //      a lower bound of its k'-th best score, since k' distinct keys reach
 //      it; its 20-bit code prefix, found bit by bit, is the threshold theta;
 //   2. the scores are formed again and the keys with s >= theta are listed in
-//      LDS (score code, ~index).  With four groups or more per kept key about
-//      1.15 k' keys reach theta; at two, 1.4 k'.
+//      LDS (score code, ~index).  Where a key's place says nothing about its
+//      score, about 1.15 k' keys reach theta with four groups per kept key, and
+//      1.4 k' with two.
 // The list is then sorted by rank (score descending, index ascending).
+//
+// Nodes stored in spatial order have their best keys side by side, in few
+// groups, and more keys reach theta the fewer groups a tile has.  So groups
+// are narrow rather than many tiles apart: pairs of rows for k <= 32 (8 max3 a
+// tile, as for any wider group) and single rows above (16 max).  Against
+// groups of four rows, same number of them (select call, us; the streaming
+// kernel in brackets): 30k nodes, 4 heads, d = 32, k = 128, 64 clusters one
+// after the other 1900 -> 681 [1755], roads along a Morton curve 1527 -> 832
+// [7338]; 100k nodes, d = 16, k = 512, clusters 11374 -> 3028 [11751]; drawn
+// positions 1278 -> 1261, 6210 -> 6172.
 // A graph whose tiles fit the waves' registers (R tiles a wave: 512 keys)
 // is scored once and its scores stay in registers between the passes.
 //
@@ -81,27 +92,27 @@ __device__ __forceinline__ uint32_t team_max(uint32_t v) {
 // use before, then the counters, thresholds and bounds, then the value buckets.
 constexpr int kValueBuckets = 64;
 
-template <int W, int T, int CAP, int QN>
+template <int W, int T, int GT, int CAP, int QN>
 constexpr size_t dense_list_bytes() {
-    const size_t lists = (size_t)QN * CAP * 8, maxima = (size_t)8 * T * W * (QN + 1) * 4;
+    const size_t lists = (size_t)QN * CAP * 8, maxima = (size_t)2 * GT * T * W * (QN + 1) * 4;
     return lists > maxima ? lists : maxima;
 }
-template <int W, int T, int CAP, int QN>
+template <int W, int T, int GT, int CAP, int QN>
 constexpr size_t dense_lds_bytes() {
-    return dense_list_bytes<W, T, CAP, QN>() + QN * (8 + 4 + 4) + (CAP > 128 ? QN * kValueBuckets * 4 : 0);
+    return dense_list_bytes<W, T, GT, CAP, QN>() + QN * (8 + 4 + 4) + (CAP > 128 ? QN * kValueBuckets * 4 : 0);
 }
 
 // R > 0: resident (graphs of at most 32 W R keys, read from K itself);
 // R == 0: two passes over the tiled keys kp.  tasks == nullptr: one graph of
 // N nodes, task b being its b-th run of 32 queries (64 for QN = 64).
-template <int D, int W, int T, int CAP, int QN, int R>
+template <int D, int W, int T, int GT, int CAP, int QN, int R>
 __global__ __launch_bounds__(64 * W) void dense_select_kernel(
     const uint4* __restrict__ kp, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
     const Task* __restrict__ tasks, int32_t ntasks, int32_t N, int32_t H, int32_t k, int32_t ntiles,
     int32_t* __restrict__ topk_idx) {
     constexpr int NC = D / 16;
     constexpr int TPQ = 64 * W / QN;          // threads per query
-    constexpr int NG = 8 * T * W;             // group maxima per query
+    constexpr int NG = 2 * GT * T * W;        // group maxima per query
     constexpr int E = CAP / TPQ;              // list entries per thread
     constexpr bool kBuckets = CAP > 128;
     constexpr int QB = QN > 32 ? QN / 32 : 1;   // blocks of 32 queries a wave scores
@@ -110,7 +121,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
     extern __shared__ uint64_t lds[];
     uint64_t* const list = lds;                                  // [QN][CAP]
     float* const gsh = reinterpret_cast<float*>(lds);            // [NG][QN + 1]
-    char* const tail = reinterpret_cast<char*>(lds) + dense_list_bytes<W, T, CAP, QN>();
+    char* const tail = reinterpret_cast<char*>(lds) + dense_list_bytes<W, T, GT, CAP, QN>();
     uint64_t* const bound = reinterpret_cast<uint64_t*>(tail);   // [QN] keys below it are not listed
     float* const theta_sh = reinterpret_cast<float*>(bound + QN);
     int32_t* const cnt = reinterpret_cast<int32_t*>(theta_sh + QN);
@@ -150,9 +161,11 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
     // multiple of 32; the resident variant's at the graph's first key).
     const int base = R > 0 ? tk.key_lo : tk.key_lo & ~31;
     const int nt = (tk.key_hi - base + 31) >> 5;
-    // Pass 1 takes every sample-th tile: theta is then about the (sample k')-th
-    // best score, and pass 2 lists sample times as many keys (1.2 sample k' <
-    // CAP).  Worth it where the tiles left out cost more than the extra listing,
+    // Pass 1 takes every sample-th tile (each wave by itself: runs of tiles left
+    // out would hide whole runs of neighbouring best keys; 45k nodes of a smooth
+    // road network in Morton order, d = 32, k = 16 1180 -> 884 us): theta is
+    // then about the (sample k')-th best score, and pass 2 lists sample times as
+    // many keys (1.2 sample k' < CAP).  Worth it where the tiles left out cost more than the extra listing,
     // which grows with k: a 100k-node graph at d = 32, k = 32 5.2 -> 4.6 ms,
     // 200k nodes at d = 16, k = 10 3.1 -> 2.5 (every third: 2.3), but 45k
     // nodes at d = 32, k = 32 1.19 -> 1.28.
@@ -193,16 +206,17 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
 
     // Scores the wave's tiles in order, PF loads ahead (the next tiles are in
     // flight while one is scored), and hands each to f(scores, tile, u), u
-    // counting the wave's tiles modulo T.
-    auto stream_tiles = [&](int step, auto f) {
+    // counting the wave's tiles modulo T.  The wave takes tiles first, first +
+    // step, ...
+    auto stream_tiles = [&](int first, int step, auto f) {
         constexpr int PF = NC >= 4 ? 1 : 2;
         constexpr int U = T > PF ? T : PF;
         static_assert(U % T == 0 && U % PF == 0, "powers of two");
-        if (wave >= nt) return;
+        if (first >= nt) return;
         uint4 ring[PF][NC];
 #pragma unroll
-        for (int p = 0; p < PF; ++p) load_tile(ring[p], min(wave + step * p, nt - 1));
-        for (int i = wave; i < nt;) {
+        for (int p = 0; p < PF; ++p) load_tile(ring[p], min(first + step * p, nt - 1));
+        for (int i = first; i < nt;) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (i < nt) {
@@ -218,20 +232,18 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
 
     // ---- 1. group maxima ----
     f32x16 kept[R > 0 ? R : 1][QB];
-    float gm[T][QB][4];
+    float gm[T][QB][GT];
 #pragma unroll
     for (int u = 0; u < T; ++u)
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) gm[u][qb][g] = -INFINITY;
-    auto add_groups = [&](const f32x16 (&a)[QB], float (&m)[QB][4]) {
+            for (int g = 0; g < GT; ++g) gm[u][qb][g] = -INFINITY;
+    auto add_groups = [&](const f32x16 (&a)[QB], float (&m)[QB][GT]) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                m[qb][g] = fmaxf(fmaxf(m[qb][g], a[qb][4 * g]),
-                                 fmaxf(fmaxf(a[qb][4 * g + 1], a[qb][4 * g + 2]), a[qb][4 * g + 3]));
+            for (int r = 0; r < 16; ++r) m[qb][r / (16 / GT)] = fmaxf(m[qb][r / (16 / GT)], a[qb][r]);
     };
     auto tile_groups = [&](const f32x16 (&a)[QB], float (&m)[QB][4]) {
 #pragma unroll
@@ -253,7 +265,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
             }
         }
     } else {
-        stream_tiles(W * sample, [&](const f32x16 (&acc)[QB], int, int u) { add_groups(acc, gm[u]); });
+        stream_tiles(wave * sample, W * sample, [&](const f32x16 (&acc)[QB], int, int u) { add_groups(acc, gm[u]); });
     }
     if (QN >= 32 || col < QN) {
 #pragma unroll
@@ -261,8 +273,8 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    gsh[(((wave * 2 + half) * T + u) * 4 + g) * (QN + 1) + 32 * qb + col] = gm[u][qb][g];
+                for (int g = 0; g < GT; ++g)
+                    gsh[(((wave * 2 + half) * T + u) * GT + g) * (QN + 1) + 32 * qb + col] = gm[u][qb][g];
     }
     if (t < QN) cnt[t] = 0;
     __syncthreads();
@@ -470,7 +482,18 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         limits(theta, bnd);
 #pragma unroll
         for (int u = 0; u < R; ++u)
-            if (wave + W * u < nt) list_tile(kept[u], gm[u], wave + W * u, theta, bnd, false);
+            if (wave + W * u < nt) {
+                float m[QB][4];
+                if constexpr (GT == 4) {
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) m[qb][g] = gm[u][qb][g];
+                } else {
+                    tile_groups(kept[u], m);
+                }
+                list_tile(kept[u], m, wave + W * u, theta, bnd, false);
+            }
     }
 #pragma unroll 1
     for (int at = 0; at < kRelist; ++at) {
@@ -478,7 +501,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
             float theta[QB];
             uint64_t bnd[QB];
             limits(theta, bnd);
-            stream_tiles(W, [&](const f32x16 (&acc)[QB], int i, int) {
+            stream_tiles(wave, W, [&](const f32x16 (&acc)[QB], int i, int) {
                 float m[QB][4];
                 tile_groups(acc, m);
                 list_tile(acc, m, i, theta, bnd, at > 0);
@@ -547,17 +570,17 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         for (int p = m + s; p < k; p += TPQ) dst[p] = -1;
 }
 
-template <int D, int W, int T, int CAP, int QN, int R>
+template <int D, int W, int T, int GT, int CAP, int QN, int R>
 hipError_t launch_dense_t(const void* kp, const void* K, const void* Q, const Task* tasks, int32_t ntasks, int32_t N,
                           int32_t H, int32_t k, int32_t ntiles, int32_t* topk_idx, hipStream_t stream) {
-    constexpr size_t lds = dense_lds_bytes<W, T, CAP, QN>();
+    constexpr size_t lds = dense_lds_bytes<W, T, GT, CAP, QN>();
     static_assert(lds <= 160 * 1024, "LDS of a gfx950 workgroup");
-    const void* fn = reinterpret_cast<const void*>(dense_select_kernel<D, W, T, CAP, QN, R>);
+    const void* fn = reinterpret_cast<const void*>(dense_select_kernel<D, W, T, GT, CAP, QN, R>);
     if (lds > 65536) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((dense_select_kernel<D, W, T, CAP, QN, R>), dim3((unsigned)((int64_t)ntasks * H * (QN < 32 ? 32 / QN : 1))),
+    hipLaunchKernelGGL((dense_select_kernel<D, W, T, GT, CAP, QN, R>), dim3((unsigned)((int64_t)ntasks * H * (QN < 32 ? 32 / QN : 1))),
                        dim3(64 * W),
                        lds, stream, reinterpret_cast<const uint4*>(kp), reinterpret_cast<const uint16_t*>(K),
                        reinterpret_cast<const uint16_t*>(Q), tasks, ntasks, N, H, k, ntiles, topk_idx);
@@ -570,27 +593,27 @@ hipError_t launch_dense_select(const void* kp, const void* K, const void* Q, con
                                int32_t N, int32_t H, int32_t d, int32_t k, int32_t ntiles, int32_t run, bool resident,
                                int32_t* topk_idx, hipStream_t stream) {
     if (ntasks <= 0) return hipSuccess;
-#define KMIP_DENSE(DD, WW, TT, CC, QQ, RR) \
-    return launch_dense_t<DD, WW, TT, CC, QQ, RR>(kp, K, Q, tasks, ntasks, N, H, k, ntiles, topk_idx, stream)
+#define KMIP_DENSE(DD, WW, TT, GG, CC, QQ, RR) \
+    return launch_dense_t<DD, WW, TT, GG, CC, QQ, RR>(kp, K, Q, tasks, ntasks, N, H, k, ntiles, topk_idx, stream)
 #define KMIP_DENSE_D(DD)                                                   \
     if (d == DD && resident && run == 32) {                                \
-        if (k <= 32) KMIP_DENSE(DD, 8, 2, 128, 32, 2);                     \
-        if (k <= 128) KMIP_DENSE(DD, 8, 2, 256, 32, 2);                    \
+        if (k <= 32) KMIP_DENSE(DD, 8, 2, 4, 128, 32, 2);                  \
+        if (k <= 128) KMIP_DENSE(DD, 8, 2, 4, 256, 32, 2);                 \
     }                                                                      \
     if (d == DD && !resident && k <= 32) {                                 \
-        if (run == 64) KMIP_DENSE(DD, 8, 2, 128, 64, 0);                   \
-        if (run == 32) KMIP_DENSE(DD, 8, 2, 128, 32, 0);                   \
+        if (run == 64) KMIP_DENSE(DD, 8, 1, 8, 128, 64, 0);                \
+        if (run == 32) KMIP_DENSE(DD, 8, 1, 8, 128, 32, 0);                \
     }                                                                      \
-    if (d == DD && !resident && k <= 128 && run == 32) KMIP_DENSE(DD, 8, 8, 256, 32, 0);
+    if (d == DD && !resident && k <= 128 && run == 32) KMIP_DENSE(DD, 8, 2, 16, 256, 32, 0);
     KMIP_DENSE_D(16)
     KMIP_DENSE_D(32)
     KMIP_DENSE_D(64)
     KMIP_DENSE_D(128)
 #undef KMIP_DENSE_D
-#define KMIP_DENSE_D(DD)                                  \
-    if (d == DD && !resident && run == 32) {              \
-        if (k <= 256) KMIP_DENSE(DD, 16, 8, 512, 32, 0);  \
-        if (k <= 512) KMIP_DENSE(DD, 16, 8, 1024, 16, 0); \
+#define KMIP_DENSE_D(DD)                                                   \
+    if (d == DD && !resident && run == 32) {                               \
+        if (k <= 256) KMIP_DENSE(DD, 16, 2, 16, 512, 32, 0);               \
+        if (k <= 512) KMIP_DENSE(DD, 16, 2, 16, 1024, 16, 0);              \
     }
     KMIP_DENSE_D(16)
     KMIP_DENSE_D(32)

@@ -40,6 +40,12 @@ CASES = [
     (4000, 1, 64, 100, [1500, 2500], "copies"),
     (31000, 1, 16, 16, None, "copies"),
     (2600, 1, 32, 300, None, "copies"),
+    # clusters one after the other: a query's best keys fill few tiles
+    (9000, 2, 32, 16, None, "runs"),
+    (45000, 1, 32, 16, None, "runs"),
+    (12000, 2, 64, 128, [5000, 7000], "runs"),
+    (12000, 1, 16, 200, None, "runs"),
+    (12000, 1, 16, 512, None, "runs"),
     # 64 queries a task; sampled first passes (every second, every third tile)
     (31000, 1, 16, 32, None, "ints"),
     (42000, 1, 16, 10, None, "ints"),
@@ -64,6 +70,8 @@ def test_rows_equal_oracle(case):
         q[rng.random(N) < 0.5] = 0
     elif kind == "copies":
         kk = kk[rng.integers(0, 50, N)]
+    elif kind == "runs":
+        kk += rng.integers(-8, 9, size=(40, H, d))[np.sort(rng.integers(0, 40, N))]
     elif kind == "sorted":
         q[:] = 1
         kk[:] = 0
