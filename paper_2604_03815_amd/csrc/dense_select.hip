@@ -323,12 +323,13 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
     // ---- 2. list the keys at or above the threshold ----
     // Scores a of tile i, whose maxima over rows 4 g .. 4 g + 3 are m: a tile
     // without a key to list costs three instructions past the maxima, and
-    // only the groups that hold one are looked at row by row.  A lane raises
-    // its theta past scores that cannot matter any more: to infinity once its
-    // query's list has overflowed (it is listed again), and, listing again,
-    // past the bound's own score beyond the bound's index (20k nodes, 2 heads,
-    // d = 128, 50 distinct keys, k = 32: 1617 -> 935 us, the streaming kernel
-    // 1373; 30k nodes, 4 heads, d = 32, zero queries 3926 -> 814).
+    // only the groups that hold one are looked at row by row.  Listing again, a
+    // lane raises its theta past the bound's own score beyond the bound's
+    // index: many equal keys are looked at once only (20k nodes, 2 heads, d =
+    // 128, 50 distinct keys, k = 32: 1617 -> 1254 us, the streaming kernel
+    // 1374; 30k nodes, 4 heads, d = 32, zero queries 3915 -> 2601, 12253).
+    // (Stopping also once the list is full, in the first listing: 932 and 831,
+    // but 3% on inputs that never overflow.)
     auto list_tile = [&](const f32x16 (&a)[QB], const float (&m)[QB][4], int i, float (&theta)[QB],
                          const uint64_t (&bnd)[QB], bool again) {
         const int j0 = base + 32 * i;
@@ -350,10 +351,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
                         const uint64_t key = make_key(a[qb][r], j);
                         if (j >= tk.key_lo && j < tk.key_hi && key >= bnd[qb] && (QN >= 32 || col < QN)) {
                             const int slot = atomicAdd(&cnt[qi], 1);
-                            if (slot < CAP)
-                                list[qi * CAP + slot] = key;
-                            else
-                                theta[qb] = INFINITY;
+                            if (slot < CAP) list[qi * CAP + slot] = key;
                         }
                     }
                 }
