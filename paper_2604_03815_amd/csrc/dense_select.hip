@@ -91,6 +91,7 @@ __device__ __forceinline__ uint32_t team_max(uint32_t v) {
 // (row stride QN + 1 words, so that a team's reads meet few bank conflicts)
 // use before, then the counters, thresholds and bounds, then the value buckets.
 constexpr int kValueBuckets = 64;
+constexpr uint32_t kWideBucket = 64;   // up to this many keys of a bucket, or half the list, are compared with each other
 
 template <int W, int T, int GT, int CAP, int QN>
 constexpr size_t dense_list_bytes() {
@@ -105,8 +106,11 @@ constexpr size_t dense_lds_bytes() {
 // R > 0: resident (graphs of at most 32 W R keys, read from K itself);
 // R == 0: two passes over the tiled keys kp.  tasks == nullptr: one graph of
 // N nodes, task b being its b-th run of 32 queries (64 for QN = 64).
+// (With lists of 256 keys the LDS holds two blocks a CU: four waves per SIMD, as
+// many as the registers are held to, at 2 to 16 spilled ones; the resident form
+// at d = 128 would spill 41 and keeps three waves.)
 template <int D, int W, int T, int GT, int CAP, int QN, int R>
-__global__ __launch_bounds__(64 * W) void dense_select_kernel(
+__global__ __launch_bounds__(64 * W, CAP == 256 && (D < 128 || R == 0) ? 4 : 1) void dense_select_kernel(
     const uint4* __restrict__ kp, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
     const Task* __restrict__ tasks, int32_t ntasks, int32_t N, int32_t H, int32_t k, int32_t ntiles,
     int32_t* __restrict__ topk_idx) {
@@ -409,11 +413,79 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
                 if (i0 + TPQ * i < m) place(e[i], rank[i], write);
         }
     };
+    // The need-th largest of the team's nonzero words w (0: none), bit by bit
+    // below the leading bits that all of them share.
+    auto kth_word = [&](const uint32_t (&w)[E], int need) {
+        uint32_t mx = 0, mnc = 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            mx = max(mx, w[i]);
+            mnc = max(mnc, w[i] != 0u ? ~w[i] : 0u);
+        }
+        mx = team_max<TPQ>(mx);
+        const uint32_t diff = mx ^ ~team_max<TPQ>(mnc);
+        const int bits = 32 - __clz(diff);
+        uint32_t x = bits == 0 ? mx : mx >> (bits - 1) >> 1 << (bits - 1) << 1;
+#pragma unroll 1
+        for (int bit = bits - 1; bit >= 0; --bit) {
+            const uint32_t y = x | (1u << bit);
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < E; ++i) c += w[i] >= y ? 1 : 0;
+            if (team_sum<TPQ>(c) >= need) x = y;
+        }
+        return x;
+    };
+    // The k-th largest of the list's m >= k keys: its code, then its ~index among
+    // the keys of that code.  (One word of each key in registers at a time: the
+    // registers decide how many waves a CU holds.)
+    auto kth_key = [&](int m) {
+        uint32_t w[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) w[i] = s + TPQ * i < m ? (uint32_t)(row[s + TPQ * i] >> 32) : 0u;
+        const uint32_t code = kth_word(w, k);
+        int above = 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) above += w[i] > code ? 1 : 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) w[i] = w[i] == code ? (uint32_t)row[s + TPQ * i] : 0u;
+        return ((uint64_t)code << 32) | kth_word(w, k - team_sum<TPQ>(above));
+    };
+    // Moves the list's keys >= b to its front and returns their number (the
+    // team's reads of a round come before its writes, which go to slots already
+    // read).
+    auto keep_from = [&](uint64_t b, int m) {
+        int run = 0;
+        for (int f0 = 0; f0 < m; f0 += TPQ) {
+            const uint64_t x = f0 + s < m ? row[f0 + s] : 0ull;
+            const bool keep = x != 0ull && x >= b;
+            const uint64_t mine = __builtin_amdgcn_ballot_w64(keep) >> (lane - s) & (~0ull >> (64 - TPQ));
+            __builtin_amdgcn_wave_barrier();
+            if (keep) row[run + __builtin_popcountll(mine & ((1ull << s) - 1ull))] = x;
+            __builtin_amdgcn_wave_barrier();
+            run += __builtin_popcountll(mine);
+        }
+        return run;
+    };
     // Rank by value buckets: bucket v holds the scores in the v-th part of
     // [lowest, highest], highest first, and the list is reordered by bucket;
     // a key's rank is the size of the buckets before its own plus the keys of
-    // its own that beat it.  Every thread of the block calls it.
+    // its own that beat it.  Where a bucket holds many keys (ties), only the k
+    // best are kept and ranked against each other.  Without `write` the k-th
+    // key is all that is wanted.  Every thread of the block calls it.  (64 graphs
+    // of 100 to 450 nodes, 3 heads, d = 32, zero queries: k = 64 947 us with all
+    // ties compared within their bucket, 112 so; k = 100 1020 and 138.)
     auto rank_buckets = [&](int m, bool write) {
+        if (!write) {
+            if (m >= k) {
+                const uint64_t b = kth_key(m);
+                if (s == 0) {
+                    bound[q] = b;
+                    theta_sh[q] = key_score(b);
+                }
+            }
+            return;
+        }
         uint64_t e[E];
         int slot[E];
         uint32_t mx = 0, mnc = 0;
@@ -435,9 +507,14 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         for (int v = s; v < kValueBuckets; v += TPQ) h[v] = 0;
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < E; ++i) slot[i] = e[i] != 0ull ? atomicAdd(&h[bucket(e[i])], 1) : 0;
+        for (int i = 0; i < E; ++i) {
+            slot[i] = s + TPQ * i;   // one score: one bucket, as the keys lie
+            if (hi > lo && e[i] != 0ull) slot[i] = atomicAdd(&h[bucket(e[i])], 1);
+        }
+        if (!(hi > lo) && s == 0) h[0] = m;
         __syncthreads();
         // exclusive sums over the buckets: the team's first 16 lanes take 4 each
+        uint32_t widest = 0;
         if (s < 16) {
             constexpr int V = kValueBuckets / 16;
             int c[V], sum = 0;
@@ -445,6 +522,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
             for (int v = 0; v < V; ++v) {
                 c[v] = h[V * s + v];
                 sum += c[v];
+                widest = max(widest, (uint32_t)c[v]);
             }
             int x = sum;
             x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
@@ -458,18 +536,25 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
                 run += c[v];
             }
         }
+        widest = team_max<TPQ>(widest);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < E; ++i)
             if (e[i] != 0ull) row[h[bucket(e[i])] + slot[i]] = e[i];
         __syncthreads();
+        if (widest > max(kWideBucket, (uint32_t)m / 2u)) {
+            rank_all(m > k ? keep_from(kth_key(m), m) : m, true);
+            return;
+        }
 #pragma unroll 1
         for (int i = s; i < m; i += TPQ) {
             const uint64_t x = row[i];
             const int v = bucket(x);
             const int f1 = v + 1 < kValueBuckets ? h[v + 1] : m;
-            int rank = h[v];
-            for (int f = rank; f < f1; ++f) rank += row[f] > x ? 1 : 0;
+            const int f0 = h[v];
+            int rank = f0;
+#pragma unroll 4
+            for (int f = f0; f < f1; ++f) rank += row[f] > x ? 1 : 0;
             place(x, rank, write);
         }
     };
@@ -482,14 +567,14 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         for (int u = 0; u < R; ++u)
             if (wave + W * u < nt) {
                 float m[QB][4];
-                if constexpr (GT == 4) {
 #pragma unroll
-                    for (int qb = 0; qb < QB; ++qb)
+                for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                        for (int g = 0; g < 4; ++g) m[qb][g] = gm[u][qb][g];
-                } else {
-                    tile_groups(kept[u], m);
-                }
+                    for (int g = 0; g < 4; ++g) {
+                        m[qb][g] = gm[u][qb][GT / 4 * g];
+#pragma unroll
+                        for (int i = 1; i < GT / 4; ++i) m[qb][g] = fmaxf(m[qb][g], gm[u][qb][GT / 4 * g + i]);
+                    }
                 list_tile(kept[u], m, wave + W * u, theta, bnd, false);
             }
     }
@@ -544,20 +629,7 @@ __global__ __launch_bounds__(64 * W) void dense_select_kernel(
         if (m > k) rank_all(m, false);
         __syncthreads();
         if (m > k) {
-            // the team's reads of a round come before its writes, which go to
-            // slots already read
-            const uint64_t bnd = bound[q];
-            int run = 0;
-            for (int f0 = 0; f0 < m; f0 += TPQ) {
-                const uint64_t x = f0 + s < m ? row[f0 + s] : 0ull;
-                const bool keep = x != 0ull && x >= bnd;
-                const uint64_t mine = __builtin_amdgcn_ballot_w64(keep) >> (lane - s) & (~0ull >> (64 - TPQ));
-                const int at = run + __builtin_popcountll(mine & ((1ull << s) - 1ull));
-                __builtin_amdgcn_wave_barrier();
-                if (keep) row[at] = x;
-                __builtin_amdgcn_wave_barrier();
-                run += __builtin_popcountll(mine);
-            }
+            const int run = keep_from(bound[q], m);
             if (s == 0) cnt[q] = run;
         }
         __syncthreads();
@@ -598,7 +670,7 @@ hipError_t launch_dense_select(const void* kp, const void* K, const void* Q, con
         if (k <= 32) KMIP_DENSE(DD, 8, 2, 4, 128, 32, 2);                  \
         if (k <= 128) KMIP_DENSE(DD, 8, 2, 4, 256, 32, 2);                 \
     }                                                                      \
-    if (d == DD && !resident && k <= 32) {                                 \
+    if (d == DD && !resident && k <= 32) {                             \
         if (run == 64) KMIP_DENSE(DD, 8, 1, 8, 128, 64, 0);                \
         if (run == 32) KMIP_DENSE(DD, 8, 1, 8, 128, 32, 0);                \
     }                                                                      \
@@ -609,7 +681,7 @@ hipError_t launch_dense_select(const void* kp, const void* K, const void* Q, con
     KMIP_DENSE_D(128)
 #undef KMIP_DENSE_D
 #define KMIP_DENSE_D(DD)                                                   \
-    if (d == DD && !resident && run == 32) {                               \
+    if (d == DD && !resident && run == 32) {                           \
         if (k <= 256) KMIP_DENSE(DD, 16, 2, 16, 512, 32, 0);               \
         if (k <= 512) KMIP_DENSE(DD, 16, 2, 16, 1024, 16, 0);              \
     }

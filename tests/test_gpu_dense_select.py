@@ -40,6 +40,10 @@ CASES = [
     (4000, 1, 64, 100, [1500, 2500], "copies"),
     (31000, 1, 16, 16, None, "copies"),
     (2600, 1, 32, 300, None, "copies"),
+    # ties in lists of more than 128 keys: all keys, a few scores, all but one
+    *[(sum(EDGES), 2, d, k, EDGES, kind) for d, k, kind in
+      ((32, 64, "zeros"), (16, 100, "zeros"), (64, 128, "zeros"), (32, 100, "spike"), (16, 64, "copies"))],
+    *[(2600, 1, 32, k, s, "spike") for k, s in ((40, None), (128, [900, 1700]), (200, None), (512, None))],
     # clusters one after the other: a query's best keys fill few tiles
     (9000, 2, 32, 16, None, "runs"),
     (45000, 1, 32, 16, None, "runs"),
@@ -68,6 +72,9 @@ def test_rows_equal_oracle(case):
     kk = rng.integers(-1, 2, size=(N, H, d)).astype(np.float32)
     if kind == "zeros":
         q[rng.random(N) < 0.5] = 0
+    elif kind == "spike":
+        kk[:] = np.where(rng.random((N, 1, 1)) < 0.01, rng.integers(1, 100, (N, 1, 1)), 0)
+        q = np.abs(q) + 1
     elif kind == "copies":
         kk = kk[rng.integers(0, 50, N)]
     elif kind == "runs":
