@@ -343,15 +343,14 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
     const kmip::SelectShape shape = choose_shape(N, H, d, k, G);
     const int32_t qb = shape.qb;
 
-    int64_t largest = N;
-    if (G > 1) {
-        largest = 0;
-        for (int32_t g = 0; g < G; ++g) {
-            const int64_t n = graph_offsets[g + 1] - graph_offsets[g];
-            if (select_path(n, N, G, H, d, k) == kPathDense) largest = std::max(largest, n);
-        }
+    // the largest graph of each path
+    int64_t largest[3] = {0, 0, 0};
+    for (int32_t g = 0; g < G; ++g) {
+        const int64_t n = G > 1 ? graph_offsets[g + 1] - graph_offsets[g] : N;
+        int64_t& most = largest[select_path(n, N, G, H, d, k)];
+        most = std::max(most, n);
     }
-    const int32_t run = dense_run(largest, d, k);
+    const int32_t run = dense_run(largest[kPathDense], d, k);
     auto step_of = [&](int path) { return path == kPathResident ? 32 : path == kPathDense ? run : 32 * qb; };
     // Tasks by path: [0, nres) resident, then ndense, then nstream.
     const kmip::Task* dtasks = nullptr;
@@ -414,7 +413,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
     }
     for (int path = kPathResident; path <= kPathDense; ++path) {
         e = kmip::launch_dense_select(kp, K, Q, dtasks, count[path], n32, H, d, k, ntiles, step_of(path),
-                                      path == kPathResident,                                      topk_idx, stream);
+                                      path == kPathResident ? (int32_t)largest[path] : 0, topk_idx, stream);
         if (e != hipSuccess) return hip_fail(e, "dense select launch");
         if (dtasks != nullptr) dtasks += count[path];
     }

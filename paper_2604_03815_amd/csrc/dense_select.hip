@@ -660,28 +660,37 @@ hipError_t launch_dense_t(const void* kp, const void* K, const void* Q, const Ta
 }  // namespace
 
 hipError_t launch_dense_select(const void* kp, const void* K, const void* Q, const Task* tasks, int32_t ntasks,
-                               int32_t N, int32_t H, int32_t d, int32_t k, int32_t ntiles, int32_t run, bool resident,
+                               int32_t N, int32_t H, int32_t d, int32_t k, int32_t ntiles, int32_t run, int32_t resident,
                                int32_t* topk_idx, hipStream_t stream) {
     if (ntasks <= 0) return hipSuccess;
 #define KMIP_DENSE(DD, WW, TT, GG, CC, QQ, RR) \
     return launch_dense_t<DD, WW, TT, GG, CC, QQ, RR>(kp, K, Q, tasks, ntasks, N, H, k, ntiles, topk_idx, stream)
+    // A resident graph has n / 4 groups of four rows, or n / 2 pairs.  Where k
+    // comes near the number of groups, the lists of more than 256 nodes
+    // overflow; where it does not, the larger number takes longer to search (up
+    // to 128 nodes every key is listed either way).
+    // 64 graphs, 3 heads, d = 32, four rows against pairs (us): about 277 nodes
+    // k = 65 81 and 74, k = 80 119 and 78; 377 nodes k = 72 101 and 102, k = 90
+    // 140 and 108; 478 nodes k = 65 115 and 122, k = 100 147 and 137.
 #define KMIP_DENSE_D(DD)                                                   \
-    if (d == DD && resident && run == 32) {                                \
+    if (d == DD && resident > 0 && run == 32) {                            \
         if (k <= 32) KMIP_DENSE(DD, 8, 2, 4, 128, 32, 2);                  \
+        if (k <= 128 && resident > 128 && resident < 5 * k)                \
+            KMIP_DENSE(DD, 8, 2, 8, 256, 32, 2);                           \
         if (k <= 128) KMIP_DENSE(DD, 8, 2, 4, 256, 32, 2);                 \
     }                                                                      \
-    if (d == DD && !resident && k <= 32) {                             \
+    if (d == DD && resident == 0 && k <= 32) {                             \
         if (run == 64) KMIP_DENSE(DD, 8, 1, 8, 128, 64, 0);                \
         if (run == 32) KMIP_DENSE(DD, 8, 1, 8, 128, 32, 0);                \
     }                                                                      \
-    if (d == DD && !resident && k <= 128 && run == 32) KMIP_DENSE(DD, 8, 2, 16, 256, 32, 0);
+    if (d == DD && resident == 0 && k <= 128 && run == 32) KMIP_DENSE(DD, 8, 2, 16, 256, 32, 0);
     KMIP_DENSE_D(16)
     KMIP_DENSE_D(32)
     KMIP_DENSE_D(64)
     KMIP_DENSE_D(128)
 #undef KMIP_DENSE_D
 #define KMIP_DENSE_D(DD)                                                   \
-    if (d == DD && !resident && run == 32) {                           \
+    if (d == DD && resident == 0 && run == 32) {                           \
         if (k <= 256) KMIP_DENSE(DD, 16, 2, 16, 512, 32, 0);               \
         if (k <= 512) KMIP_DENSE(DD, 16, 2, 16, 1024, 16, 0);              \
     }

@@ -117,12 +117,12 @@ size_t select_lds_bytes(int32_t k, SelectShape shape);
 // Score + select without pruning (dense_select.hip; same results as
 // launch_select).  Tasks hold at most `run` queries, 32 or (two passes, k <= 32)
 // 64; tasks == nullptr: one graph of N nodes, task b its b-th run.  resident:
-// every graph holds at most kResidentGraph nodes, k <= 128, and the keys are
-// read from K (kp may be NULL); else from the tiled keys kp.  k <= 512 for
-// d <= 64 and k <= 128 for d = 128.
+// the nodes of the largest graph, at most kResidentGraph, where k <= 128 and the
+// keys are read from K (kp may be NULL); or 0, and the keys are read from the
+// tiled keys kp.  k <= 512 for d <= 64 and k <= 128 for d = 128.
 constexpr int kResidentGraph = 512;
 hipError_t launch_dense_select(const void* kp, const void* K, const void* Q, const Task* tasks, int32_t ntasks,
-                               int32_t N, int32_t H, int32_t d, int32_t k, int32_t ntiles, int32_t run, bool resident,
+                               int32_t N, int32_t H, int32_t d, int32_t k, int32_t ntiles, int32_t run, int32_t resident,
                                int32_t* topk_idx, hipStream_t stream);
 
 // Query grouping by direction (group.hip): reference directions per head.

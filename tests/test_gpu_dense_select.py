@@ -27,10 +27,13 @@ def _dev(a):
 
 
 EDGES = [1, 31, 32, 33, 0, 480, 511, 512, 513, 700]   # tiles, and the 512-key register path
+BIG = [257, 288, 300, 320, 385, 460, 512]             # more nodes than a list of 256 keys takes
 CASES = [
     # (N, H, d, k, sizes, inputs)
     *[(sum(EDGES), 2, d, k, EDGES, "ints") for d, k in ((16, 1), (32, 32), (64, 33), (128, 16), (128, 128), (32, 128))],
     *[(2733, 1, 32, k, [600, 31, 2, 2100], "ints") for k in (129, 256, 257, 512)],
+    # graphs of few groups per kept key: four rows a group, pairs
+    *[(sum(BIG), 2, d, k, BIG, "ints") for d, k in ((32, 64), (16, 80), (32, 100), (64, 103), (128, 112))],
     (512, 3, 32, 16, None, "ints"),
     (513, 3, 32, 16, None, "ints"),
     # lists that overflow: zero queries (every key ties), keys in order of score
