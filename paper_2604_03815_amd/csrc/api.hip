@@ -189,11 +189,7 @@ enum SelectPath { kPathResident = 0, kPathDense = 1, kPathStream = 2 };
 // streaming kernel, whose waves keep to the same tiles, is as fast.  Above
 // k = 128 the streaming kernel's trees leave room for one or two waves per
 // CU (k = 256, 200k nodes, 2 heads, d = 16: 27 against 14 ms).
-// A dense launch has a workgroup per 32 queries and head (N, G: nodes and
-// graphs of the whole call), kept below 2^31 threads: more (many heads of a
-// few nodes) go to the persistent grid of the streaming kernel.
-SelectPath select_path(int64_t n, int64_t N, int32_t G, int32_t H, int32_t d, int32_t k) {
-    if ((N / 32 + G) * H > (int64_t(1) << (k > KMIP_MAX_K_WIDE ? 20 : 22))) return kPathStream;
+SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
     if (n <= kmip::kResidentGraph && k <= KMIP_MAX_K_WIDE) return kPathResident;
     int64_t most = 65536;
     if (k > KMIP_MAX_K_WIDE)
@@ -215,7 +211,7 @@ SelectPath select_path(int64_t n, int64_t N, int32_t G, int32_t H, int32_t d, in
 // whichever path takes it.)
 bool sized_for_grouping(int64_t N, int32_t G, int32_t d) { return G == 1 && N >= 8192 && d <= 64; }
 bool use_grouping(int64_t N, int32_t G, int32_t H, int32_t d, int32_t k) {
-    return sized_for_grouping(N, G, d) && select_path(N, N, G, H, d, k) == kPathStream;
+    return sized_for_grouping(N, G, d) && select_path(N, G, H, d, k) == kPathStream;
 }
 
 // Queries per dense task: 64 share each key tile's load once the scan outweighs
@@ -347,7 +343,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
     int64_t largest[3] = {0, 0, 0};
     for (int32_t g = 0; g < G; ++g) {
         const int64_t n = G > 1 ? graph_offsets[g + 1] - graph_offsets[g] : N;
-        int64_t& most = largest[select_path(n, N, G, H, d, k)];
+        int64_t& most = largest[select_path(n, G, H, d, k)];
         most = std::max(most, n);
     }
     const int32_t run = dense_run(largest[kPathDense], d, k);
@@ -365,7 +361,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
             const size_t first = tasks.size();
             for (int32_t g = 0; g < G; ++g) {
                 const int32_t lo = graph_offsets[g], hi = graph_offsets[g + 1];
-                if (select_path(hi - lo, N, G, H, d, k) != path) continue;
+                if (select_path(hi - lo, G, H, d, k) != path) continue;
                 const int32_t step = step_of(path);
                 for (int32_t q0 = lo; q0 < hi; q0 += step)
                     tasks.push_back(kmip::Task{q0, std::min(step, hi - q0), lo, hi});
@@ -380,7 +376,7 @@ kmip_status_t kmip_topk_with_events(const void* Q, const void* K, const int32_t*
         if (e != hipSuccess) return hip_fail(e, "work list upload");
         dtasks = reinterpret_cast<const kmip::Task*>(dst);
     } else {
-        const SelectPath path = select_path(N, N, G, H, d, k);
+        const SelectPath path = select_path(N, G, H, d, k);
         const int32_t step = step_of(path);
         count[path] = (int32_t)((N + step - 1) / step);
     }

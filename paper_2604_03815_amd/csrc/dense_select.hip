@@ -112,7 +112,7 @@ constexpr size_t dense_lds_bytes() {
 template <int D, int W, int T, int GT, int CAP, int QN, int R>
 __global__ __launch_bounds__(64 * W, CAP == 256 && (D < 128 || R == 0) ? 4 : 1) void dense_select_kernel(
     const uint4* __restrict__ kp, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
-    const Task* __restrict__ tasks, int32_t ntasks, int32_t N, int32_t H, int32_t k, int32_t ntiles,
+    const Task* __restrict__ tasks, int32_t ntasks, int32_t N, int32_t H, int32_t k, int32_t ntiles, int32_t first,
     int32_t* __restrict__ topk_idx) {
     constexpr int NC = D / 16;
     constexpr int TPQ = 64 * W / QN;          // threads per query
@@ -137,8 +137,9 @@ __global__ __launch_bounds__(64 * W, CAP == 256 && (D < 128 || R == 0) ? 4 : 1) 
     // tasks hold runs of at most 32 QB queries: QN = 16 takes one in two blocks
     constexpr int kRun = 32 * QB, kSub = kRun / QN;
     const int nblk = ntasks * kSub;
-    const int head = blockIdx.x / nblk;
-    const int b = blockIdx.x - head * nblk;
+    const int block = first + blockIdx.x;
+    const int head = block / nblk;
+    const int b = block - head * nblk;
     Task tk = tasks != nullptr ? tasks[b / kSub] : Task{b / kSub * kRun, min(kRun, N - b / kSub * kRun), 0, N};
     if constexpr (kSub > 1) {
         tk.q_begin += b % kSub * QN;
@@ -650,11 +651,20 @@ hipError_t launch_dense_t(const void* kp, const void* K, const void* Q, const Ta
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((dense_select_kernel<D, W, T, GT, CAP, QN, R>), dim3((unsigned)((int64_t)ntasks * H * (QN < 32 ? 32 / QN : 1))),
-                       dim3(64 * W),
-                       lds, stream, reinterpret_cast<const uint4*>(kp), reinterpret_cast<const uint16_t*>(K),
-                       reinterpret_cast<const uint16_t*>(Q), tasks, ntasks, N, H, k, ntiles, topk_idx);
-    return hipGetLastError();
+    // Many heads of a few nodes: slices of at most 2^31 threads (fewer than 2^28
+    // blocks in all, as N H < 2^27)
+    constexpr int64_t kSlice = (int64_t(1) << 31) / (64 * W);
+    const int64_t blocks = (int64_t)ntasks * H * (QN < 32 ? 32 / QN : 1);
+    for (int64_t first = 0; first < blocks; first += kSlice) {
+        hipLaunchKernelGGL((dense_select_kernel<D, W, T, GT, CAP, QN, R>),
+                           dim3((unsigned)(blocks - first < kSlice ? blocks - first : kSlice)), dim3(64 * W), lds, stream,
+                           reinterpret_cast<const uint4*>(kp), reinterpret_cast<const uint16_t*>(K),
+                           reinterpret_cast<const uint16_t*>(Q), tasks, ntasks, N, H, k, ntiles, (int32_t)first,
+                           topk_idx);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

@@ -153,3 +153,27 @@ def test_tile_by_tile_walk(case):
     sel = sample_rows(N, 1, 512, seed=5)
     o_idx, _, _ = oracle.topk(oracle.from_bf16(qb), oracle.from_bf16(kb), k, offsets=off, sel=sel)
     np.testing.assert_array_equal(got[sel], o_idx)
+
+
+def test_more_blocks_than_a_launch_holds():
+    # Graphs of two nodes (one and none among them) with many heads: more
+    # workgroups than one launch of 2^31 threads, so the last heads come from
+    # a second launch.  Small integers: scores are exact and tie.
+    H, d, k = 66000, 16, 2
+    sizes = [2] * 60 + [1, 0] * 5
+    N = sum(sizes)
+    assert sum(s > 0 for s in sizes) * H * 512 > 2**31
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(63)
+    q, kk = (torch.randint(-2, 3, (N, H, d), generator=gen, device=DEV, dtype=torch.int8).to(torch.bfloat16) for _ in range(2))
+    print(f"[case] dense select slices N={N} H={H} d={d} k={k}", flush=True)
+    idx = kmip.topk(q, kk, k, graph_offsets=np.concatenate([[0], np.cumsum(sizes)]))
+    torch.cuda.synchronize()
+    a = torch.arange(0, 120, 2, device=DEV)
+    for i in (0, 1):
+        s = [(q[a + i].float() * kk[a + j].float()).sum(-1) for j in (0, 1)]
+        first = torch.where(s[0] >= s[1], 0, 1) + a[:, None]
+        assert torch.equal(idx[a + i, :, 0], first.int())
+        assert torch.equal(idx[a + i, :, 1], (2 * a[:, None] + 1 - first).int())
+    one = torch.arange(120, N, device=DEV)
+    assert (idx[one, :, 0] == one[:, None]).all() and (idx[one, :, 1] == -1).all()
