@@ -691,13 +691,16 @@ __device__ __forceinline__ int32_t wave_rank(int32_t* ctr, int32_t digit) {
 // interleaved copy, row u, lie side by side, so the reduction's gathers for
 // one key row mostly read neighbouring rows and share cache lines.  The
 // records carry u as their query row.
-// (Four waves per SIMD where that costs few spills: k <= 16 at d = 32 62 -> 58
-// us in a batch of 128 graphs, k = 128 at d = 64 737 -> 655 at 262k nodes;
-// at d = 32, k = 32 it would cost 57 spilled registers, 285 -> 485 us.)
+// (Four waves per SIMD where that costs few spills: k <= 16 at d = 32, d_V <=
+// 32 62 -> 58 us in a batch of 128 graphs, k = 128 at d = 64 737 -> 655 at 262k
+// nodes.  At d = 32, k = 32 it would cost 57 spilled registers, 285 -> 485 us; at
+// d = 32, k = 16 and d_V = 64 or 128 45, the whole backward of 100k nodes, 4
+// heads 578 against 500 and 770 against 689, of 64 graphs of about 270 nodes,
+// 3 heads, d_V = 64 111 against 97.)
 constexpr int split_threads(int ns) { return ns <= 8 ? 256 : 2048 / ns; }
 
 template <int D, int DV, int NS>
-__global__ __launch_bounds__(split_threads(NS), D <= 64 && (NS == 8 || (NS == 1 && D == 32)) ? 4 : 1) void coef_split_kernel(
+__global__ __launch_bounds__(split_threads(NS), D <= 64 && (NS == 8 || (NS == 1 && D == 32 && DV <= 32)) ? 4 : 1) void coef_split_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const uint16_t* __restrict__ dO, const int32_t* __restrict__ idx, const float* __restrict__ lse,
     const int32_t* __restrict__ perm, int32_t N, int32_t H, int32_t k, float scale, float* __restrict__ dQ,
