@@ -972,8 +972,8 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
 //      query row of the interleaved head-major copy (q then dO) is one 16-byte
 //      load per lane; the lanes of q add a*q to dK, those of dO p*dO to dV,
 //      four records' rows in flight.  A key row whose
-//      records all lie in the span is stored (added with atomics where the
-//      bucket has several pieces); the row a span starts in the middle of and
+//      records all lie in the span is stored, or, where the bucket has several
+//      pieces, added with atomics; the row a span starts in the middle of and
 //      the one it ends in go to LDS;
 //   3. these partial rows, in row order, are added up sixteen at a time, an
 //      atomic per element where the row changes (dK and dV are zero at the
@@ -982,10 +982,29 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
 // phases of a workgroup on small ones.  Against sixteen-lane teams on 8192
 // records that added every run with atomics (us): 128 graphs, d = 32, k = 16
 // 117 -> 46; 16 clouds, d = 32, k = 32 178 -> 87; 100k nodes, d = 32 480 -> 321;
-// 262k nodes, d = 64, k = 128 1605 -> 1155; 500k nodes, d = 16 1072 -> 1115.
+// 262k nodes, d = 64, k = 128 1577 -> 1124; 500k nodes, d = 16 1029 -> 988.
+// The atomics of several pieces go to neighbouring addresses from neighbouring
+// lanes (eight addresses 32 bytes apart before; us): 84k nodes, 16 heads, d = 32,
+// k = 20, normal rows (two pieces a bucket) 2025 -> 756, plain stores in their
+// place 683; 760k nodes, d = 32, k = 50 1255 -> 791; 200k nodes, 2 heads, d = 32,
+// k = 64 493 -> 465; 30k nodes, 4 heads, d = 32, k = 256 606 -> 515.
 // (Sums in LDS with float atomics instead of the sort were six times slower:
 // an LDS float add took about four clocks a lane.)
 constexpr int kSumThreads = 512;
+
+// Exchanges bit M of the register index with bit M of the lane.
+template <int M>
+__device__ __forceinline__ void exchange_bit(float (&a)[8], int lane) {
+    const bool hi = (lane & M) != 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if ((e & M) != 0) continue;
+        const float give = hi ? a[e] : a[e | M];
+        float got;
+        if constexpr (M == 1) got = step_partner<1>(give); else got = xor_lane<M>(give);
+        if (hi) a[e] = got; else a[e | M] = got;
+    }
+}
 
 constexpr int pow2_at_least(int x) { return x <= 1 ? 1 : 2 * pow2_at_least((x + 1) / 2); }
 
@@ -1002,6 +1021,7 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
     constexpr int B = 4;                       // records of a group in flight
     constexpr int PER = kPiece / kSumThreads;  // records per thread in the sort
     constexpr int SEG = 16;                    // partial rows summed by one thread
+    constexpr int T = LG < 8 ? LG : 8;         // lanes that exchange a row's sums
     static_assert(2 * GR * RW * sizeof(float) <= kPiece * sizeof(BucketRecord), "partial rows fit the records' area");
     static_assert(kSumThreads / (8 * LG) * SEG == 2 * GR, "every partial row has its threads");
     static_assert(kMaxBucketRows <= kSumThreads, "one counter a thread in the scan");
@@ -1077,14 +1097,24 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
             } else if (f1 > p1) {
                 row1 = cur;   // the last row: its sums stay in acc
                 return;
-            } else if (!used) {
             } else if (alone) {
-                float4* d4 = reinterpret_cast<float4*>(dst + cur * width);
-                d4[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-                d4[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+                if (used) {
+                    float4* d4 = reinterpret_cast<float4*>(dst + cur * width);
+                    d4[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                    d4[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+                }
             } else {
+                // the elements of T lanes are exchanged so that an atomic's
+                // neighbouring lanes add to neighbouring addresses
+                if constexpr (T == 8) exchange_bit<4>(acc, c);
+                exchange_bit<2>(acc, c);
+                exchange_bit<1>(acc, c);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) atomicAdd(dst + cur * width + e, acc[e]);
+                for (int e = 0; e < 8; ++e) {
+                    const int el = 8 * ((c & ~(T - 1)) + (e & (T - 1))) + (e & ~(T - 1)) + (c & (T - 1));
+                    const size_t row = ((size_t)lo << shift) + cur;
+                    if (el < RW) atomicAdd(el < D ? dK + row * D + el : dV + row * DV + (el - D), acc[e]);
+                }
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0f;

@@ -32,6 +32,8 @@ CASES = [(70, 2, d, dv, k) for d, dv, k in (
 # more than 2^20 pairs at d = 128 and k > 128, 2^16 at unequal widths: the bucketed
 # reduction's forms for them (k up to 256 and 512: 8 and 4 teams a workgroup)
 CASES += [(3001, 3, 128, 128, 128), (2100, 2, 32, 64, 16), (2051, 3, 64, 16, 20), (2060, 1, 16, 128, 40), (2050, 2, 32, 32, 300), (2100, 4, 64, 64, 129), (4099, 2, 16, 16, 512)]
+# several pieces of 4096 pairs a bucket, row groups of 4 to 32 lanes, some of them idle
+CASES += [(2060, 1, 16, 16, 40), (2060, 1, 16, 32, 40), (2060, 1, 32, 16, 64), (2060, 1, 16, 64, 33), (2060, 1, 64, 32, 128), (2060, 1, 64, 128, 100), (2060, 1, 128, 64, 128)]
 # by head (wide rows, large k; a partly filled last workgroup per head)
 CASES += [(1025, 3, 32, 32, 257), (1030, 2, 16, 16, 512), (1024, 3, 128, 128, 16), (1025, 3, 64, 64, 20)]
 
