@@ -8,7 +8,9 @@
 //
 // Mapping: a team of 16 lanes per (query, head), 16 teams per workgroup (4 for
 // k > 128).  Rows are read by D/8 lanes each (gather.h), 128/D rows per team
-// and step.  The team's key indices go to LDS first; a step's lanes form
+// and step.  The team's key indices go to LDS first, and the slots after the
+// last one kept are left out (graphs of fewer than k nodes: 85 nodes, 8 heads, d =
+// 64, k = 512 53 us with them, 16 without); a step's lanes form
 // their rows' scores, which go to LDS beside the indices; the softmax runs
 // with the slots on lanes (slot = lane + 16 s); and the value rows are gathered
 // with the weights read back from LDS.  A team lies within a wave, whose LDS
@@ -18,7 +20,10 @@
 // trips and, where the rows of a head do not stay in L2, the fabric.  Against a
 // lane per row (us): 262k nodes, d = 64, k = 128 925 -> 340; 100k nodes, 4
 // heads, d = 32, k = 32 241 -> 162; 500k nodes, 4 heads, d = 16, k = 32 520 ->
-// 420; a batch of 128 graphs, d = 32, k = 16 37 -> 22.
+// 420; a batch of 128 graphs, d = 32, k = 16 37 -> 22.  (Below about 3,000
+// query-heads, where the chip is mostly idle, a team's chain of steps counts, and
+// many slots take longer than a lane per row did: 931 nodes, d = 32, k = 128 8.6
+// and 11.9.)
 //
 // Attention dropout (keep != nullptr): slot t's weight in the sum is
 // multiplied by keep_scale when keep[qh k + t] is nonzero and by 0
@@ -37,12 +42,30 @@
 namespace kmip {
 namespace {
 
-// Words between the LDS areas of two teams: {index, score or weight} of every
-// slot (k rounded up to 16), and 16 words so that the four teams of a wave
-// meet different banks.
-__host__ __device__ constexpr int attend_stride(int k) { return 2 * ((k + 15) / 16 * 16) + 16; }
+// Steps whose loads go out together: the rows of S slots, at least one step
+// and, at 16 slots, at most 8 loads a lane.
+constexpr int round_steps(int s, int rpt) {
+    const int u = s > rpt ? s / rpt : 1;
+    return s == 16 && u > 8 ? 8 : u;
+}
 
-template <int D, int DV>
+// Slots a team's area holds: k rounded up to whole rounds.
+template <int S>
+__host__ __device__ constexpr int slots_of(int k) {
+    constexpr int r = S > 16 ? S : 16;
+    return (k + r - 1) / r * r;
+}
+
+// Words between the LDS areas of two teams: {index, score or weight} of every
+// slot, and 16 words so that the four teams of a wave meet different banks.
+template <int S>
+__host__ __device__ constexpr int attend_stride(int k) {
+    return 2 * slots_of<S>(k) + 16;
+}
+
+constexpr int kIdxLoads = 4;   // index loads of a lane in flight
+
+template <int D, int DV, int S>
 __global__ __launch_bounds__(256) void attend_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const int32_t* __restrict__ idx, const uint8_t* __restrict__ keep, float keep_scale, int32_t N,
@@ -62,31 +85,47 @@ __global__ __launch_bounds__(256) void attend_kernel(
         if (qh >= (int64_t)N * H) return;  // whole team exits together
         h = (int)(qh % H);
     }
-    int2* const sh = reinterpret_cast<int2*>(lds + (size_t)team * attend_stride(k));
-    const int k16 = (k + 15) / 16 * 16;
-    for (int slot = tl; slot < k16; slot += 16) {
-        const int32_t j = slot < k ? idx[(size_t)qh * k + slot] : -1;
-        sh[slot].x = j >= 0 && j < N ? j : -1;
+    int2* const sh = reinterpret_cast<int2*>(lds + (size_t)team * attend_stride<S>(k));
+    auto put = [&](int slot, int32_t j) {
+        const bool kept = j >= 0 && j < N;
+        sh[slot].x = kept ? j : -1;
+        return kept;
+    };
+    int last = k;   // slots past it are not looked at
+    if (k <= 16) {
+        put(tl, tl < k ? idx[(size_t)qh * k + tl] : -1);
+    } else {
+        last = 0;
+        for (int s0 = tl; s0 < slots_of<S>(k); s0 += 16 * kIdxLoads) {
+            int32_t j[kIdxLoads];
+#pragma unroll
+            for (int u = 0; u < kIdxLoads; ++u) j[u] = s0 + 16 * u < k ? idx[(size_t)qh * k + s0 + 16 * u] : -1;
+#pragma unroll
+            for (int u = 0; u < kIdxLoads; ++u)
+                if (s0 + 16 * u < slots_of<S>(k) && put(s0 + 16 * u, j[u])) last = s0 + 16 * u + 1;
+        }
+        last = (int)group16_max((float)last);   // (at most 512)
     }
     __builtin_amdgcn_wave_barrier();
 
     using KS = RowSplit<D>;
     using VS = RowSplit<DV>;
+    constexpr int KU = round_steps(S, KS::RPT), VU = round_steps(S, VS::RPT);
     {
         float q[8];
         widen8(q, *reinterpret_cast<const uint4*>(Q + (size_t)qh * D + 8 * (tl & (KS::LPR - 1))));
         const int g = tl / KS::LPR;
         const uint16_t* kcol = K + (size_t)h * D + 8 * (tl & (KS::LPR - 1));
-        for (int s0 = 0; s0 < k16; s0 += KS::RPT * KS::U) {
-            int32_t j[KS::U];
-            uint4 w[KS::U];
+        for (int s0 = 0; s0 < last; s0 += KS::RPT * KU) {
+            int32_t j[KU];
+            uint4 w[KU];
 #pragma unroll
-            for (int u = 0; u < KS::U; ++u) {
+            for (int u = 0; u < KU; ++u) {
                 j[u] = sh[s0 + KS::RPT * u + g].x;
                 w[u] = *reinterpret_cast<const uint4*>(kcol + (size_t)(j[u] >= 0 ? j[u] : 0) * ((size_t)H * D));
             }
 #pragma unroll
-            for (int u = 0; u < KS::U; ++u) {
+            for (int u = 0; u < KU; ++u) {
                 const float z = scale * row_lanes_sum<KS::LPR>(dot8(q, w[u]));
                 if ((tl & (KS::LPR - 1)) == 0) sh[s0 + KS::RPT * u + g].y = __float_as_int(j[u] >= 0 ? z : -INFINITY);
             }
@@ -97,21 +136,21 @@ __global__ __launch_bounds__(256) void attend_kernel(
     // The first value rows go out before the softmax.
     const int g = tl / VS::LPR;
     const uint16_t* vcol = V + (size_t)h * DV + 8 * (tl & (VS::LPR - 1));
-    auto value_rows = [&](uint4 (&w)[VS::U], int s0) {
+    auto value_rows = [&](uint4 (&w)[VU], int s0) {
 #pragma unroll
-        for (int u = 0; u < VS::U; ++u) {
+        for (int u = 0; u < VU; ++u) {
             const int32_t j = sh[s0 + VS::RPT * u + g].x;
             w[u] = *reinterpret_cast<const uint4*>(vcol + (size_t)(j >= 0 ? j : 0) * ((size_t)H * DV));
         }
     };
-    uint4 w[VS::U];
+    uint4 w[VU];
     value_rows(w, 0);
 
     float zmax = -INFINITY;
-    for (int slot = tl; slot < k16; slot += 16) zmax = fmaxf(zmax, __int_as_float(sh[slot].y));
+    for (int slot = tl; slot < last; slot += 16) zmax = fmaxf(zmax, __int_as_float(sh[slot].y));
     zmax = group16_max(zmax);
     float zs = 0.0f;
-    for (int slot = tl; slot < k16; slot += 16) {
+    for (int slot = tl; slot < last; slot += 16) {
         const int2 e = sh[slot];
         float p = e.x >= 0 ? __expf(__int_as_float(e.y) - zmax) : 0.0f;
         zs += p;
@@ -126,12 +165,12 @@ __global__ __launch_bounds__(256) void attend_kernel(
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
     for (int s0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < VS::U; ++u) {
+        for (int u = 0; u < VU; ++u) {
             const int2 e = sh[s0 + VS::RPT * u + g];
             if (e.x >= 0) axpy8(acc, __int_as_float(e.y), w[u]);
         }
-        s0 += VS::RPT * VS::U;
-        if (s0 >= k16) break;
+        s0 += VS::RPT * VU;
+        if (s0 >= last) break;
         value_rows(w, s0);
     }
     scatter_rows_sum<DV>(acc, tl);
@@ -151,7 +190,12 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     // 16 teams a workgroup; with more than 128 slots a team's LDS area would
     // leave few of them per CU, so a workgroup is one wave
     const int teams = k > 128 ? 4 : 16;
-    const size_t lds = (size_t)teams * attend_stride(k) * sizeof(int32_t);
+    // Slots a round: up to four where there are no more (258k nodes, 2 heads, d =
+    // 64, k = 1 87 -> 56 us; 16k nodes, 8 heads, d = 16, k = 1 14.9 -> 14.3); past
+    // 256, where the LDS holds two or three waves per SIMD, 64 (d = 16, 12.5k nodes, 4
+    // heads, k = 512 263 -> 178; 51k nodes, d = 32 325 -> 266), but at wider rows that
+    // costs more registers than it gains (d = 64, 326k nodes, k = 512 2829 and 2941).
+    const int round = k <= 4 ? 4 : k > 256 && d <= 32 && dv <= 32 ? 64 : 16;
     const int32_t per_head = (N + teams - 1) / teams, head_blocks = perm == nullptr && gather_by_head(N, H, d, dv, k, one_graph) ? per_head : 0;
     const dim3 blocks = perm != nullptr   ? dim3((unsigned)per_head, (unsigned)H)
                         : head_blocks > 0 ? dim3((unsigned)((int64_t)per_head * H))
@@ -159,11 +203,18 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     const uint16_t* q = reinterpret_cast<const uint16_t*>(Q);
     const uint16_t* kk = reinterpret_cast<const uint16_t*>(K);
     const uint16_t* v = reinterpret_cast<const uint16_t*>(V);
-#define KMIP_ATTEND_CASE(DD, DVV)                                                              \
-    if (d == DD && dv == DVV) {                                                                \
-        hipLaunchKernelGGL((attend_kernel<DD, DVV>), blocks, dim3(16 * teams), lds, stream, q, kk, v, idx, keep,  \
-                           keep_scale, N, H, k, scale, perm, head_blocks, out, lse);           \
-        return hipGetLastError();                                                              \
+#define KMIP_ATTEND_ROUND(DD, DVV, SS)                                                                         \
+    if (round == SS) {                                                                                         \
+        hipLaunchKernelGGL((attend_kernel<DD, DVV, SS>), blocks, dim3(16 * teams),                             \
+                           teams * attend_stride<SS>(k) * sizeof(int32_t), stream, q, kk, v, idx, keep, keep_scale, \
+                           N, H, k, scale, perm, head_blocks, out, lse);                                       \
+        return hipGetLastError();                                                                              \
+    }
+#define KMIP_ATTEND_CASE(DD, DVV)       \
+    if (d == DD && dv == DVV) {         \
+        KMIP_ATTEND_ROUND(DD, DVV, 4)   \
+        KMIP_ATTEND_ROUND(DD, DVV, 16)  \
+        if constexpr (DD <= 32 && DVV <= 32) KMIP_ATTEND_ROUND(DD, DVV, 64) \
     }
 #define KMIP_ATTEND_D(DD) \
     KMIP_ATTEND_CASE(DD, 16) KMIP_ATTEND_CASE(DD, 32) KMIP_ATTEND_CASE(DD, 64) KMIP_ATTEND_CASE(DD, 128)
@@ -173,6 +224,7 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     KMIP_ATTEND_D(128)
 #undef KMIP_ATTEND_D
 #undef KMIP_ATTEND_CASE
+#undef KMIP_ATTEND_ROUND
     return hipErrorInvalidValue;
 }
 
