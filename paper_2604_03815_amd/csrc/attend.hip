@@ -7,7 +7,7 @@
 // same routine the backward uses, so the weights of the two passes agree.
 //
 // Mapping: a team of 16 lanes per (query, head), 16 teams per workgroup (4 for
-// k > 128).  Rows are read by D/8 lanes each (gather.h), 128/D rows per team
+// k > 128), or four teams that share its rounds.  Rows are read by D/8 lanes each (gather.h), 128/D rows per team
 // and step.  The team's key indices go to LDS first, and the slots after the
 // last one kept are left out (graphs of fewer than k nodes: 85 nodes, 8 heads, d =
 // 64, k = 512 53 us with them, 16 without); a step's lanes form
@@ -20,10 +20,7 @@
 // trips and, where the rows of a head do not stay in L2, the fabric.  Against a
 // lane per row (us): 262k nodes, d = 64, k = 128 925 -> 340; 100k nodes, 4
 // heads, d = 32, k = 32 241 -> 162; 500k nodes, 4 heads, d = 16, k = 32 520 ->
-// 420; a batch of 128 graphs, d = 32, k = 16 37 -> 22.  (Below about 3,000
-// query-heads, where the chip is mostly idle, a team's chain of steps counts, and
-// many slots take longer than a lane per row did: 931 nodes, d = 32, k = 128 8.6
-// and 11.9.)
+// 420; a batch of 128 graphs, d = 32, k = 16 37 -> 22.
 //
 // Attention dropout (keep != nullptr): slot t's weight in the sum is
 // multiplied by keep_scale when keep[qh k + t] is nonzero and by 0
@@ -63,16 +60,36 @@ __host__ __device__ constexpr int attend_stride(int k) {
     return 2 * slots_of<S>(k) + 16;
 }
 
+// Maximum and sum over the lanes of P teams.
+template <int P>
+__device__ __forceinline__ float teams_max(float v) {
+    v = group16_max(v);
+#pragma unroll
+    for (int m = 16; m < 16 * P; m <<= 1) v = fmaxf(v, __shfl_xor(v, m));
+    return v;
+}
+
+template <int P>
+__device__ __forceinline__ float teams_sum(float v) {
+    v = group16_sum(v);
+#pragma unroll
+    for (int m = 16; m < 16 * P; m <<= 1) v += __shfl_xor(v, m);
+    return v;
+}
+
 constexpr int kIdxLoads = 4;   // index loads of a lane in flight
 
-template <int D, int DV, int S>
+template <int D, int DV, int S, int P>
 __global__ __launch_bounds__(256) void attend_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     const int32_t* __restrict__ idx, const uint8_t* __restrict__ keep, float keep_scale, int32_t N,
     int32_t H, int32_t k, float scale, const int32_t* __restrict__ perm, int32_t head_blocks, float* __restrict__ out,
     float* __restrict__ lse) {
     extern __shared__ int32_t lds[];
-    const int tl = threadIdx.x & 15, team = threadIdx.x >> 4, teams = blockDim.x >> 4;
+    // P teams share a query-head: team `part` takes every P-th round
+    constexpr int TL = 16 * P;
+    const int tl = threadIdx.x & 15, team = threadIdx.x / TL, teams = blockDim.x / TL;
+    const int part = P > 1 ? (threadIdx.x >> 4) & (P - 1) : 0, pl = threadIdx.x & (TL - 1);
     int64_t qh;
     int h;
     if (perm != nullptr || head_blocks > 0) {
@@ -93,18 +110,21 @@ __global__ __launch_bounds__(256) void attend_kernel(
     };
     int last = k;   // slots past it are not looked at
     if (k <= 16) {
-        put(tl, tl < k ? idx[(size_t)qh * k + tl] : -1);
+        if (P == 1 || part == 0) put(tl, tl < k ? idx[(size_t)qh * k + tl] : -1);
     } else {
         last = 0;
-        for (int s0 = tl; s0 < slots_of<S>(k); s0 += 16 * kIdxLoads) {
+        for (int s0 = pl; s0 < slots_of<S>(k); s0 += TL * kIdxLoads) {
             int32_t j[kIdxLoads];
 #pragma unroll
-            for (int u = 0; u < kIdxLoads; ++u) j[u] = s0 + 16 * u < k ? idx[(size_t)qh * k + s0 + 16 * u] : -1;
+            for (int u = 0; u < kIdxLoads; ++u) {
+                const int slot = s0 + TL * u;
+                j[u] = slot < k ? idx[(size_t)qh * k + slot] : -1;
+            }
 #pragma unroll
             for (int u = 0; u < kIdxLoads; ++u)
-                if (s0 + 16 * u < slots_of<S>(k) && put(s0 + 16 * u, j[u])) last = s0 + 16 * u + 1;
+                if (s0 + TL * u < slots_of<S>(k) && put(s0 + TL * u, j[u])) last = s0 + TL * u + 1;
         }
-        last = (int)group16_max((float)last);   // (at most 512)
+        last = (int)teams_max<P>((float)last);   // (at most 512)
     }
     __builtin_amdgcn_wave_barrier();
 
@@ -116,7 +136,7 @@ __global__ __launch_bounds__(256) void attend_kernel(
         widen8(q, *reinterpret_cast<const uint4*>(Q + (size_t)qh * D + 8 * (tl & (KS::LPR - 1))));
         const int g = tl / KS::LPR;
         const uint16_t* kcol = K + (size_t)h * D + 8 * (tl & (KS::LPR - 1));
-        for (int s0 = 0; s0 < last; s0 += KS::RPT * KU) {
+        for (int s0 = part * KS::RPT * KU; s0 < last; s0 += P * KS::RPT * KU) {
             int32_t j[KU];
             uint4 w[KU];
 #pragma unroll
@@ -144,34 +164,41 @@ __global__ __launch_bounds__(256) void attend_kernel(
         }
     };
     uint4 w[VU];
-    value_rows(w, 0);
+    int s0 = part * VS::RPT * VU;
+    value_rows(w, P == 1 || s0 < last ? s0 : 0);
 
     float zmax = -INFINITY;
-    for (int slot = tl; slot < last; slot += 16) zmax = fmaxf(zmax, __int_as_float(sh[slot].y));
-    zmax = group16_max(zmax);
+    for (int slot = pl; slot < last; slot += TL) zmax = fmaxf(zmax, __int_as_float(sh[slot].y));
+    zmax = teams_max<P>(zmax);
     float zs = 0.0f;
-    for (int slot = tl; slot < last; slot += 16) {
+    for (int slot = pl; slot < last; slot += TL) {
         const int2 e = sh[slot];
         float p = e.x >= 0 ? __expf(__int_as_float(e.y) - zmax) : 0.0f;
         zs += p;
         if (keep != nullptr && e.x >= 0) p *= keep[(size_t)qh * k + slot] != 0 ? keep_scale : 0.0f;
         sh[slot].y = __float_as_int(p);
     }
-    zs = group16_sum(zs);
+    zs = teams_sum<P>(zs);
     __builtin_amdgcn_wave_barrier();
 
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-    for (int s0 = 0;;) {
+    while (s0 < last) {
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
             const int2 e = sh[s0 + VS::RPT * u + g];
             if (e.x >= 0) axpy8(acc, __int_as_float(e.y), w[u]);
         }
-        s0 += VS::RPT * VU;
-        if (s0 >= last) break;
-        value_rows(w, s0);
+        s0 += P * VS::RPT * VU;
+        if (s0 < last) value_rows(w, s0);
+    }
+    if constexpr (P > 1) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int m = 16; m < TL; m <<= 1) acc[e] += __shfl_xor(acc[e], m);
+        if (part != 0) return;
     }
     scatter_rows_sum<DV>(acc, tl);
     const bool any = zmax != -INFINITY;
@@ -189,13 +216,22 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     if (nqh == 0) return hipSuccess;
     // 16 teams a workgroup; with more than 128 slots a team's LDS area would
     // leave few of them per CU, so a workgroup is one wave
-    const int teams = k > 128 ? 4 : 16;
+    // Four teams (a wave, a workgroup) share a query-head while there are few of
+    // them, since a team's chain of rounds takes longer than the chip's work
+    // (one team, four; a lane per row in brackets; us): 931 nodes, d = 32, k = 128
+    // 12.1, 6.4 [9.3]; 2,082 nodes, d = 32, k = 200 18.1, 9.6 [12.7]; 1,192 nodes, 4
+    // heads, d = 128, k = 50 16.7, 12.6 [28.6]; 6,088 nodes, d = 16, k = 128 10.5,
+    // 10.5 [10.3]; 7,575 nodes, 2 heads, d = 32, k = 64 10.5, 13.4 [18.0]; past 128
+    // slots 9,768 nodes, d = 32, d_V = 64, k = 256 34.6, 26.7 [60.5]; 14,318 nodes, d =
+    // 16, k = 200 26.4, 28.8 [26.3].
+    const int parts = k > 32 && nqh <= (k > 128 ? 12288 : 6144) ? 4 : 1;
+    const int teams = parts > 1 ? 1 : k > 128 ? 4 : 16;
     // Slots a round: up to four where there are no more (258k nodes, 2 heads, d =
     // 64, k = 1 87 -> 56 us; 16k nodes, 8 heads, d = 16, k = 1 14.9 -> 14.3); past
     // 256, where the LDS holds two or three waves per SIMD, 64 (d = 16, 12.5k nodes, 4
     // heads, k = 512 263 -> 178; 51k nodes, d = 32 325 -> 266), but at wider rows that
     // costs more registers than it gains (d = 64, 326k nodes, k = 512 2829 and 2941).
-    const int round = k <= 4 ? 4 : k > 256 && d <= 32 && dv <= 32 ? 64 : 16;
+    const int round = k <= 4 ? 4 : k > 256 && d <= 32 && dv <= 32 && parts == 1 ? 64 : 16;
     const int32_t per_head = (N + teams - 1) / teams, head_blocks = perm == nullptr && gather_by_head(N, H, d, dv, k, one_graph) ? per_head : 0;
     const dim3 blocks = perm != nullptr   ? dim3((unsigned)per_head, (unsigned)H)
                         : head_blocks > 0 ? dim3((unsigned)((int64_t)per_head * H))
@@ -203,18 +239,19 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     const uint16_t* q = reinterpret_cast<const uint16_t*>(Q);
     const uint16_t* kk = reinterpret_cast<const uint16_t*>(K);
     const uint16_t* v = reinterpret_cast<const uint16_t*>(V);
-#define KMIP_ATTEND_ROUND(DD, DVV, SS)                                                                         \
-    if (round == SS) {                                                                                         \
-        hipLaunchKernelGGL((attend_kernel<DD, DVV, SS>), blocks, dim3(16 * teams),                             \
+#define KMIP_ATTEND_ROUND(DD, DVV, SS, PP)                                                                     \
+    if (round == SS && parts == PP) {                                                                          \
+        hipLaunchKernelGGL((attend_kernel<DD, DVV, SS, PP>), blocks, dim3(16 * PP * teams),                    \
                            teams * attend_stride<SS>(k) * sizeof(int32_t), stream, q, kk, v, idx, keep, keep_scale, \
                            N, H, k, scale, perm, head_blocks, out, lse);                                       \
         return hipGetLastError();                                                                              \
     }
 #define KMIP_ATTEND_CASE(DD, DVV)       \
     if (d == DD && dv == DVV) {         \
-        KMIP_ATTEND_ROUND(DD, DVV, 4)   \
-        KMIP_ATTEND_ROUND(DD, DVV, 16)  \
-        if constexpr (DD <= 32 && DVV <= 32) KMIP_ATTEND_ROUND(DD, DVV, 64) \
+        KMIP_ATTEND_ROUND(DD, DVV, 4, 1)   \
+        KMIP_ATTEND_ROUND(DD, DVV, 16, 1)  \
+        KMIP_ATTEND_ROUND(DD, DVV, 16, 4)  \
+        if constexpr (DD <= 32 && DVV <= 32) KMIP_ATTEND_ROUND(DD, DVV, 64, 1) \
     }
 #define KMIP_ATTEND_D(DD) \
     KMIP_ATTEND_CASE(DD, 16) KMIP_ATTEND_CASE(DD, 32) KMIP_ATTEND_CASE(DD, 64) KMIP_ATTEND_CASE(DD, 128)

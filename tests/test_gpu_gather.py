@@ -76,12 +76,16 @@ def test_given_sets(case):
             allclose_report(f"{name} v{variant}", a.cpu().numpy(), r)
 
 
-@pytest.mark.parametrize("d,dv,k", [(16, 16, 4), (64, 128, 3), (16, 32, 5), (128, 16, 9), (32, 32, 64), (128, 128, 40),
-                                    (32, 64, 17), (16, 16, 257), (16, 32, 300), (32, 16, 512), (64, 64, 400)])
-def test_rows_that_end_early(d, dv, k):
+@pytest.mark.parametrize("N,d,dv,k", [
+    (14, 16, 16, 4), (12, 64, 128, 3), (16, 16, 32, 5), (24, 128, 16, 9), (40, 32, 64, 17),
+    # up to 6144 query-heads (12288 past k = 128), four teams share one where k > 32; 64 slots a round past k = 256
+    (70, 64, 32, 33), (134, 32, 32, 64), (86, 128, 128, 40), (520, 16, 16, 257), (806, 64, 64, 400), (3072, 16, 64, 100),
+    (3073, 16, 64, 100), (3100, 32, 32, 64), (6144, 32, 64, 129), (6145, 32, 64, 129), (6150, 16, 32, 300), (6150, 32, 16, 512),
+    (6150, 64, 16, 257)])
+def test_rows_that_end_early(N, d, dv, k):
     # the aggregate looks at a row's slots up to the last one kept, a few, 16 or
     # 64 at a time: rows that keep their first 0, 1, .. slots, with holes
-    N, H = 2 * k + 6, 2
+    H = 2
     rng = np.random.default_rng(d + dv + k)
     w = workloads.iid(N, H, d, k, seed=d + dv + k, dv=dv)
     step = np.array([s for s in range(1, N) if np.gcd(s, N) == 1])   # distinct keys in a row
@@ -89,7 +93,7 @@ def test_rows_that_end_early(d, dv, k):
     idx[np.arange(k) >= (np.arange(N) % (k + 1))[:, None, None] + np.zeros((N, H, 1), int)] = -1
     idx[rng.random(idx.shape) < 0.1] = -1
     keep = (rng.random(idx.shape) >= 0.25).astype(np.uint8)
-    print(f"[case] gather, short rows d={d} dv={dv} k={k}", flush=True)
+    print(f"[case] gather, short rows N={N} d={d} dv={dv} k={k}", flush=True)
     q, kk, v = _dev(w.q), _dev(w.kk), _dev(w.v)
     out, lse = kmip.attend(q, kk, v, torch.from_numpy(idx).to(DEV), w.scale, keep=torch.from_numpy(keep).to(DEV), drop_rate=0.25)
     ro, rl = oracle.attend(*(oracle.from_bf16(a) for a in (w.q, w.kk, w.v)), idx, w.scale, keep=keep, drop_rate=0.25)
