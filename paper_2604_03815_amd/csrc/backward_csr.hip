@@ -86,7 +86,7 @@ __device__ __forceinline__ void coef_fetch(const uint16_t* __restrict__ Q, const
 // words so that the four teams of a wave meet different banks.
 __host__ __device__ constexpr size_t coef_area(int ns) { return (size_t)ns * 16 * 12 + 64; }
 
-template <int D, int DV, int NS>
+template <int D, int DV, int NS, int KEEP_REGS>
 __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* __restrict__ K,
                                           const uint16_t* __restrict__ V, const uint8_t* __restrict__ keep,
                                           float keep_scale, int32_t H, int32_t k, float scale, int tl, char* area,
@@ -96,7 +96,7 @@ __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* 
     using VS = RowSplit<DV>;
     constexpr int K16 = 16 * NS;
     constexpr int KST = K16 / KS::RPT;            // steps over the key rows
-    constexpr bool kKeep = 4 * KST <= 32;         // key rows kept in registers for dQ, else read again
+    constexpr bool kKeep = 4 * KST <= KEEP_REGS;  // key rows kept in registers for dQ, else read again
     float2* const sd = reinterpret_cast<float2*>(area);        // [K16] s, dp; then .x = g
     int32_t* const js = reinterpret_cast<int32_t*>(sd + K16);  // [K16]
     const int64_t qh = in.qh;
@@ -112,11 +112,16 @@ __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* 
     widen8(q, in.qw);
     widen8(g, in.gw);
     const bool live = in.l != -INFINITY;
+    // Rows that are read twice are read up to the last slot kept (70 nodes, 8
+    // heads, d = 64, k = 512 48 -> 15 us).
+    int last = kKeep ? K16 : 0;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         jj[s] = in.j[s];
         js[tl + 16 * s] = live ? in.j[s] : -1;
+        if (!kKeep && live && in.j[s] >= 0) last = tl + 16 * s + 1;
     }
+    if constexpr (!kKeep) last = (int)group16_max((float)last);   // (at most 512)
     __builtin_amdgcn_wave_barrier();
     const int gk = tl / KS::LPR, gv = tl / VS::LPR;
     const uint16_t* kcol = K + (size_t)h * D + 8 * (tl & (KS::LPR - 1));
@@ -155,11 +160,11 @@ __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* 
         for (int i0 = 0; i0 < KST; i0 += KS::U) dots(i0, [&](int u, const uint4& w) { kw[i0 + u] = w; });
     } else {
 #pragma unroll 1
-        for (int i0 = 0; i0 < KST; i0 += KS::U) dots(i0, [](int, const uint4&) {});
+        for (int i0 = 0; KS::RPT * i0 < last; i0 += KS::U) dots(i0, [](int, const uint4&) {});
     }
     if constexpr (DV != D) {
 #pragma unroll 1
-        for (int i0 = 0; i0 < K16 / VS::RPT; i0 += VS::U) {
+        for (int i0 = 0; VS::RPT * i0 < last; i0 += VS::U) {
             uint4 b[VS::U];
 #pragma unroll
             for (int u = 0; u < VS::U; ++u) b[u] = value_row(js[VS::RPT * (i0 + u) + gv]);
@@ -209,7 +214,7 @@ __device__ __forceinline__ void coef_team(const CoefIn<NS>& in, const uint16_t* 
             if (js[KS::RPT * i + gk] >= 0) axpy8(acc, sd[KS::RPT * i + gk].x, kw[i]);
     } else {
 #pragma unroll 1
-        for (int i0 = 0; i0 < KST; i0 += KS::U) {
+        for (int i0 = 0; KS::RPT * i0 < last; i0 += KS::U) {
             int32_t j[KS::U];
             uint4 w[KS::U];
 #pragma unroll
@@ -248,7 +253,12 @@ __global__ __launch_bounds__(256) void csr_coef_kernel(
     coef_fetch<D, DV, NS>(Q, dO, idx, lse, N, k, true, qh, tl, in);
     int32_t jj[NS];
     float ca[NS], cp[NS];
-    coef_team<D, DV, NS>(in, K, V, keep, keep_scale, H, k, scale, tl,
+    // Key rows in up to 64 registers (32 in the fused pass, whose records take
+    // the rest).  With 32 (us): 760k nodes, d = 32, k = 50, normal rows 1769 ->
+    // 1215 (a lane per row 1391 in the fused pass); 200k nodes, 2 heads, d = 32, k =
+    // 64, city 446 -> 392; 100k nodes, 4 heads, d = 64, k = 32, normal rows 674 -> 481.
+    constexpr int kKeepRegs = NS <= 4 ? 64 : 32;
+    coef_team<D, DV, NS, kKeepRegs>(in, K, V, keep, keep_scale, H, k, scale, tl,
                          reinterpret_cast<char*>(lds) + team * coef_area(NS), dQ, nullptr, 0, jj, ca, cp);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -744,7 +754,7 @@ __global__ __launch_bounds__(split_threads(NS), D <= 64 && (NS == 8 || (NS == 1 
             const int64_t v = u + TEAMS;
             coef_fetch<D, DV, NS>(Q, dO, idx, lse, N, k, v < nh, (int64_t)qrow[it + 1] * H + (v < nh ? v / N : 0), tl, nxt);
         }
-        coef_team<D, DV, NS>(cur, K, V, keep, keep_scale, H, k, scale, tl, area, dQ, QGt, (size_t)u, jj, ca, cp);
+        coef_team<D, DV, NS, 32>(cur, K, V, keep, keep_scale, H, k, scale, tl, area, dQ, QGt, (size_t)u, jj, ca, cp);
 #pragma unroll
         for (int s2 = 0; s2 < NS; ++s2) {
             const int r = it * NS + s2;
