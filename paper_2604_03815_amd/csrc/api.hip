@@ -186,7 +186,14 @@ enum SelectPath { kPathResident = 0, kPathDense = 1, kPathStream = 2 };
 // pre-passes weigh less (per head beyond the first, 45k nodes at d = 32: 157
 // against 224 us, 30k: 127 against 137).  At d = 128 and in a batch
 // nothing is pruned, but past 64k nodes the keys leave the L2 and the
-// streaming kernel, whose waves keep to the same tiles, is as fast.  Above
+// streaming kernel, whose waves keep to the same tiles, is as fast.  Wide keys
+// (d = 128, or 64 in a batch) leave it sooner where k > 32, since a block then
+// holds 32 queries, and up to k = 64 the streaming kernel's trees are still
+// small (dense against streaming, us; 4 heads, d = 128: 36k nodes, k = 33 3661 and
+// 3710, 40k 4357 and 4023, 64k 10742 and 8253; k = 50 6662 and 6712 at 50k, 10867
+// and 8913 at 64k; k = 64 6856 and 7880, 10894 and 10499; one head, k = 33 1494
+// and 1735 at 45k, 1855 and 1858 at 50k; two graphs of 60k, 4 heads, d = 64, k =
+// 33 9216 and 7226, four of 30k, 8 heads 9836 and 9691).  Above
 // k = 128 the streaming kernel's trees leave room for one or two waves per
 // CU (k = 256, 200k nodes, 2 heads, d = 16: 27 against 14 ms).
 SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
@@ -200,6 +207,8 @@ SelectPath select_path(int64_t n, int32_t G, int32_t H, int32_t d, int32_t k) {
         most = H <= 8 ? 46000 : 30000;
     else if (G == 1 && d == 64)
         most = 32768;
+    else if (d >= 64 && k > 32 && k < 64)
+        most = G == 1 && H == 1 ? 49152 : 32768;
     return n <= most ? kPathDense : kPathStream;
 }
 

@@ -64,6 +64,9 @@ CASES = [
     (65537, 1, 16, 10, None, "ints"),
     (65700, 1, 16, 16, [100, 65600], "ints"),
     (200001, 1, 16, 130, None, "ints"),
+    # wide keys, 32 < k < 64: a graph on either side of the line in one batch
+    (65600, 1, 64, 40, [32768, 32769, 63], "ints"),
+    (33200, 2, 128, 33, [400, 32800], "ints"),
 ]
 
 

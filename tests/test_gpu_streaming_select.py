@@ -43,7 +43,9 @@ class PathProbe:
 
 @pytest.mark.parametrize("N,H,d,k,streams", [
     (300, 2, 16, 8, False), (9000, 2, 64, 128, False), (65536, 1, 16, 32, False), (65537, 1, 16, 32, True),
-    (65536, 1, 128, 16, False), (65537, 1, 128, 16, True)])
+    (65536, 1, 128, 16, False), (65537, 1, 128, 16, True),
+    # 32 < k < 64 at d = 128
+    (32768, 2, 128, 33, False), (32769, 2, 128, 33, True), (32769, 2, 128, 64, False), (49152, 1, 128, 63, False), (49153, 1, 128, 63, True)])
 def test_probe_tells_the_paths_apart(N, H, d, k, streams):
     p = PathProbe(N, H, d, k)
     q = torch.randn(N, H, d, device=DEV).bfloat16()
@@ -70,7 +72,7 @@ REAL = [
     ("points", 65600, 8, 16, 32), ("points", 65600, 8, 16, 16), ("iid", 65600, 8, 16, 16),
     ("far", 65792, 2, 16, 32),
     ("iid", 200100, 1, 16, 200), ("iid", 200003, 1, 32, 400),                         # trees of 256 and 512 leaves
-    ("iid", 65601, 1, 128, 100),                                                      # neither grouped nor bounded
+    ("iid", 65601, 1, 128, 100), ("iid", 33001, 2, 128, 40),                          # neither grouped nor bounded
 ]
 
 
