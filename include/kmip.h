@@ -265,8 +265,7 @@ kmip_status_t kmip_bwd(const void* Q, const void* K, const void* V, const void* 
  * f_j = 1/(1 - drop_rate) for a kept slot and 0 for a dropped one, dV_j gets
  * p_j f_j dOut_i and f_j dp_j replaces dp_j in D_i and g_j).
  * KMIP_BWD_BUCKETED needs dv == d (else KMIP_ERR_UNSUPPORTED and workspace
- * size 0): its interleaved copy of q_i and dOut_i assumes equal widths;
- * KMIP_BWD_AUTO then runs the bucketed reduction in its form for unequal
+ * size 0), as it always has; KMIP_BWD_AUTO then runs the bucketed reduction in its form for unequal
  * widths (more than 2^16 pairs, N*H <= 8192*512), or KMIP_BWD_SEGMENTED, also
  * where the workspace passed holds only that one's arrays.  kmip_bwd and
  * kmip_bwd_workspace_size are the case dv = d, keep = NULL.

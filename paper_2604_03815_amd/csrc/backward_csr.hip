@@ -508,8 +508,8 @@ __global__ __launch_bounds__(256) void csr_reduce_kernel(
 // ---- Variant 4: pairs bucketed by blocks of key rows, sorted in LDS ----
 //
 // The key rows are cut into buckets of RB consecutive rows, at most
-// kMaxBuckets of them: RB = 4096 / d, doubled (up to kMaxBucketRows) while
-// N*H would need more buckets.  The pairs are counting-sorted by bucket only: a
+// kMaxBuckets of them: RB = 256 at d = 16, 128 at d = 32 and 64 above, doubled
+// (up to kMaxBucketRows) while N*H would need more buckets.  The pairs are counting-sorted by bucket only: a
 // counting pass takes ranges of consecutive pairs and counts them with an
 // LDS histogram over the buckets, one global atomic per bucket it touches
 // (against one per key row and workgroup for the full sort, whose per-row
@@ -1202,9 +1202,8 @@ size_t bwd_bucket_workspace_bytes(int32_t N, int32_t H, int32_t d, int32_t dv, i
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t nh = (size_t)N * H, pairs = nh * k;
     const size_t nbk = (nh + ((size_t)1 << bucket_shift((int64_t)nh, d)) - 1) >> bucket_shift((int64_t)nh, d);
-    const size_t nb = (nbk + 1 + kScanBlock - 1) / kScanBlock;
     return al(pairs * sizeof(BucketRecord)) + 3 * al((nbk + 1) * sizeof(int32_t)) +
-           al((nb + 1) * sizeof(int32_t)) + al(nh * (d + dv) * sizeof(uint16_t)) + al(pairs * sizeof(PairRecord)) +
+           al(nh * (d + dv) * sizeof(uint16_t)) + al(pairs * sizeof(PairRecord)) +
            3 * al((kMaxSup + 1) * sizeof(int32_t)) + al(group_workspace_bytes(N, H, d));
 }
 
@@ -1220,7 +1219,6 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     const int32_t rb = 1 << shift;
     const int32_t nbk = (int32_t)((nh + rb - 1) / rb);
     if (nbk > kMaxBuckets) return hipErrorInvalidValue;
-    const int32_t nb = (nbk + 1 + kScanBlock - 1) / kScanBlock;
     char* p = reinterpret_cast<char*>(ws);
     BucketRecord* rec = reinterpret_cast<BucketRecord*>(p);
     p += al(pairs * sizeof(BucketRecord));
@@ -1230,7 +1228,6 @@ hipError_t launch_bwd_bucket(const void* Q, const void* K, const void* V, const 
     p += al(((size_t)nbk + 1) * sizeof(int32_t));
     int32_t* pstart = reinterpret_cast<int32_t*>(p);   // pieces per bucket, then their starts
     p += al(((size_t)nbk + 1) * sizeof(int32_t));
-    p += al(((size_t)nb + 1) * sizeof(int32_t));
     uint16_t* qg = reinterpret_cast<uint16_t*>(p);   // q and dO interleaved, row h N + p for query perm[h][p]
     p += al((size_t)nh * (d + dv) * sizeof(uint16_t));
     PairRecord* mid = reinterpret_cast<PairRecord*>(p);   // records in super-bucket order (pass 1)

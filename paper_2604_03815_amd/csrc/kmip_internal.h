@@ -131,16 +131,16 @@ constexpr int kGroupCenters = 256;
 // Workspace bytes launch_group_queries needs.
 size_t group_workspace_bytes(int32_t N, int32_t H, int32_t d);
 
-// Groups the queries of each head by direction into ws and describes the
-// result in *out.
 // The query order [H][N] a grouping workspace holds after
 // launch_group_queries (the same address QueryGroups::perm was given).
 const int32_t* group_perm_in(const void* ws, int32_t N, int32_t H, int32_t d);
+// Groups the queries of each head by direction into ws and describes the
+// result in *out.
 hipError_t launch_group_queries(const void* Q, int32_t N, int32_t H, int32_t d, void* ws,
                                 QueryGroups* out, hipStream_t stream);
 
 // Gather-softmax-aggregate: Q, K [N,H,d] (d = d_K), V and out [N,H,dv]
-// (dv = d_V), each in {16, 32, 64}.
+// (dv = d_V), each in {16, 32, 64, 128}.
 // keep / keep_scale: attention dropout draws uint8 [N,H,k] and 1/(1 - rate),
 // or nullptr (no dropout), for this launcher and the backward ones.
 hipError_t launch_attend(const void* Q, const void* K, const void* V, const int32_t* idx,
