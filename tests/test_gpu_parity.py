@@ -93,17 +93,16 @@ def test_small_cases_full(case):
 
 @pytest.mark.parametrize("n,d,k", [(8193, 16, 32), (12345, 32, 16), (9001, 64, 128)])
 def test_key_tree_odd_sizes_full(n, d, k):
-    # Single graphs just above the size from which the keys are stored in
-    # tree order: nodes of odd sizes, a partial last superblock, and both the
-    # per-level splits and the levels finished in LDS.  Full comparison.
+    # Single graphs of odd sizes, in two dense passes.  (The key tree's odd sizes
+    # are in test_gpu_streaming_select.py.)  Full comparison.
     w = workloads.iid(n, 2, d, k, seed=n + d)
     _check_all(w, _run(w))
 
 
 def test_identical_keys_tree():
-    # Every key row equal: every projection ties, so each split of the key
-    # tree is decided by the tie count alone, and every score of a query
-    # ties, so every query keeps keys 0 .. k-1 in that order.
+    # Every key row equal: every score of a query ties, so every query keeps
+    # keys 0 .. k-1 in that order.  (For the key tree, whose splits the tie count
+    # alone then decides, see test_gpu_streaming_select.py.)
     N, H, d, k = 20000, 2, 32, 16
     rng = np.random.default_rng(3)
     row = rng.standard_normal((1, H, d)).astype(np.float32)
@@ -171,9 +170,8 @@ def test_exact_ties_integer_inputs(d):
     np.testing.assert_array_equal(res["idx"], o_idx)
 
 
-# Block-diagonal batches of graphs of at most 480 nodes go to the small-graph
-# select (scores of a whole graph in LDS, threshold by bisection, order by
-# rank); larger graphs of the same batch to the streaming kernel.  Integer
+# Block-diagonal batches of graphs of up to 512 nodes, whose scores stay in
+# registers (threshold by bisection, order by rank).  Integer
 # inputs make ties everywhere, so rows must match the oracle's index for
 # index (tie rule and order included).
 SMALL_GRAPH_BATCHES = [
@@ -343,12 +341,11 @@ def test_full_size(cfg, sample):
     print(f"c{cfg}: {sets} query-heads with the oracle's set, {loose} near-tied with a valid set")
 
 
-# The select shape bench.py times at N=500k (two query blocks of 32 per wave,
-# four candidate slots per lane) is the one the library picks when k <= 32,
-# ceil(N/64)*H >= 8192 and there is one graph.  These graphs reach it at
-# sizes where every query-head can be compared: point-cloud features (keys
-# stored in tree order, pruned by bounds, seeded thresholds) and i.i.d.
-# normal rows (most superblocks scanned).
+# Many heads: the streaming kernel's shape bench.py times at N=500k (two query
+# blocks of 32 per wave, for k <= 32 and ceil(N/64)*H >= 8192) would be picked
+# here, but the dense passes take graphs of this size; the shape itself is run
+# in test_gpu_streaming_select.py.  Every query-head of point-cloud features and
+# i.i.d. normal rows is compared.
 TWO_BLOCK = [
     ("points", 8192, 64, 32), ("points", 12288, 48, 16), ("iid", 8192, 64, 32), ("iid", 12288, 48, 16),
 ]
@@ -366,8 +363,8 @@ def test_two_block_shape_full(kind, n, h, k):
 
 
 def test_two_block_shape_integer_ties():
-    # Integer rows: every fp32 score is exact and ties abound, so the two-block
-    # shape must give the oracle's rows index for index (tie rule included).
+    # Integer rows: every fp32 score is exact and ties abound, so the rows must
+    # be the oracle's, index for index (tie rule included).
     N, H, d, k = 8192, 64, 16, 32
     rng = np.random.default_rng(8192)
     q = rng.integers(-2, 3, size=(N, H, d)).astype(np.float32)
@@ -383,9 +380,9 @@ def test_two_block_shape_integer_ties():
 
 def test_pruning_margin_far_clusters():
     # Keys in 64 tight clusters far from the origin: centre components
-    # ~ N(0, 20^2) (|c| about 80), spread 0.004 before rounding to bf16, so a
-    # superblock's ball radius is dominated by the |c| 2^-12 term of its
-    # rounding margin rather than by the spread of its keys.  Full comparison
+    # ~ N(0, 20^2) (|c| about 80), spread 0.004 before rounding to bf16 (past the
+    # dense passes' sizes, in test_gpu_streaming_select.py, the rounding margin
+    # then dominates a superblock's radius).  Full comparison
     # of every query-head; ties inside a cluster leave many near-tied rows.
     N, H, d, k = 16384, 2, 16, 32
     rng = np.random.default_rng(64)
@@ -449,7 +446,7 @@ VALUE_WIDTH = [
     (2500, 3, 32, 64, 32, None),
     (1800, 2, 64, 16, 24, [900, 0, 900]),
     (2100, 1, 32, 16, 128, [2100]),
-    (20000, 2, 16, 64, 32, None),       # one graph above the grouping size
+    (20000, 2, 16, 64, 32, None),
 ]
 
 
@@ -518,10 +515,9 @@ def test_peak_memory_linear_in_n():
 
 
 def test_fwd_grouped_order_matches_separate_calls():
-    # kmip_fwd on one grouped graph takes the aggregate in the grouped query
-    # order; the rows must be those of kmip_topk + kmip_attend, bit for bit,
-    # and the recorded events must bracket the select kernel and the
-    # aggregate in that order.
+    # The rows of kmip_fwd must be those of kmip_topk + kmip_attend, bit for bit,
+    # and the recorded events must bracket the select kernel and the aggregate in
+    # that order.  (A graph grouped by direction: test_gpu_streaming_select.py.)
     w = workloads.iid(12000, 2, 16, 16, seed=12)
     q, k, v = _dev(w.q), _dev(w.kk), _dev(w.v)
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(3)]
@@ -537,12 +533,11 @@ def test_fwd_grouped_order_matches_separate_calls():
 
 @pytest.mark.parametrize("k", [1, 8, 16])
 def test_small_graph_lists_and_full_rows_in_one_wave(k):
-    # The small-graph select lists, per query, the keys that reach a lower
-    # bound of its k-th best (k <= 16) and selects on the list when at most
-    # 112 keys do; otherwise it searches all of the row.  Here a quarter of
-    # the queries are zero (every score ties at 0: all n keys reach the
-    # bound, so n > 112 takes the full row) next to queries with integer
-    # rows (short lists), so the four queries of a wave mix both paths.
+    # The dense select lists, per query, the keys that reach a lower bound of
+    # its k-th best, at most 128, and lists a block again where a list
+    # overflows.  Here a quarter of the queries are zero (every score ties at 0:
+    # all n keys reach the bound, so n > 128 overflows) next to queries with
+    # integer rows (short lists), so a block mixes both.
     # Integer inputs make the scores exact: every row, order included, must
     # be the oracle's.
     rng = np.random.default_rng(77 + k)

@@ -39,7 +39,7 @@ DROPOUT = [
     (2000, 2, 16, 16, 16, 0.5, [700, 1300]),
     (3000, 1, 32, 32, 32, 0.1, None),
     (1500, 3, 64, 32, 8, 0.3, [1, 0, 1499]),
-    (20000, 2, 16, 16, 32, 0.5, None),     # grouped select, bucketed backward
+    (20000, 2, 16, 16, 32, 0.5, None),     # bucketed backward
 ]
 
 

@@ -1,9 +1,9 @@
 """Larger k (up to 512) and wider heads (d_K = 128) on the GPU against the
 float64 oracle.
 
-k > 128 gives the select kernel loser trees of 256 or 512 leaves (8 or 9
-levels, up to 132 KB of LDS per wave); d_K = 128 streams key tiles of eight
-16-dimension chunks.  Every case compares the index set of every query-head
+k > 128 gives the dense select lists of 512 or 1024 keys, d_K = 128 key tiles of
+eight 16-dimension chunks (the streaming kernel at these k and d, from 200,001
+and 65,537 nodes, is in test_gpu_streaming_select.py).  Every case compares the index set of every query-head
 with the oracle, out and lse on every query-head, and every backward variant
 built for the sizes (the bucketed one is not: it must refuse them).
 """
@@ -32,14 +32,14 @@ def _dev(a):
 
 WIDE = [
     # (N, H, d, dv, k, sizes)
-    (3000, 1, 16, 16, 129, None),                              # trees of 256 leaves
+    (3000, 1, 16, 16, 129, None),                              # lists of 512 keys
     (5000, 2, 32, 32, 256, None),
-    (4000, 1, 64, 64, 512, None),                              # 512 leaves, 132 KB of LDS
-    (9000, 2, 16, 16, 200, None),                              # grouped, pruned, lower-bound pass
-    (10000, 1, 32, 32, 400, None),                             # grouped, pruned
-    (2000, 2, 16, 32, 300, [1, 299, 300, 301, 480, 619]),      # batch: n < k graphs, small graphs streamed
+    (4000, 1, 64, 64, 512, None),                              # lists of 1024 keys
+    (9000, 2, 16, 16, 200, None),
+    (10000, 1, 32, 32, 400, None),
+    (2000, 2, 16, 32, 300, [1, 299, 300, 301, 480, 619]),      # batch: n < k graphs
     (3000, 1, 128, 128, 16, None),
-    (12000, 1, 128, 64, 128, None),                            # N >= 8192 but not grouped at d = 128
+    (12000, 1, 128, 64, 128, None),
     (1500, 2, 128, 16, 100, [100, 400, 1000]),
     (2500, 3, 128, 128, 1, None),
 ]
@@ -74,7 +74,7 @@ def test_wide_sizes_full(case):
 
 
 @pytest.mark.parametrize("N,d,k,sizes", [
-    (6000, 16, 300, [5000, 600, 400]),   # k > 128: the tie rule in trees of 512 leaves
+    (6000, 16, 300, [5000, 600, 400]),
     (3000, 128, 128, None),
 ])
 def test_wide_integer_ties_exact(N, d, k, sizes):

@@ -46,7 +46,8 @@ def _noalloc_via_abi(q, k, v, kk, scale):
 
 
 @pytest.mark.parametrize("first,second", [
-    ((4, 60_000, 16, 32), (4, 3_000, 16, 32)),        # grouped + key order, then the plain path
+    ((4, 70_000, 16, 32), (4, 3_000, 16, 32)),        # grouped + key order, then two dense passes
+    ((4, 60_000, 16, 32), (4, 3_000, 16, 32)),        # two dense passes, both sizes
     ((5, 40_000, None, None), (1, None, None, None)),  # d = 64, k = 128, then config 1 (d = 32)
 ])
 def test_noalloc_matches_fwd_twice(first, second):
