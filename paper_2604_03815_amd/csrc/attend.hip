@@ -227,11 +227,14 @@ hipError_t launch_attend(const void* Q, const void* K, const void* V, const int3
     const int parts = k > 32 && nqh <= (k > 128 ? 12288 : 6144) ? 4 : 1;
     const int teams = parts > 1 ? 1 : k > 128 ? 4 : 16;
     // Slots a round: up to four where there are no more (258k nodes, 2 heads, d =
-    // 64, k = 1 87 -> 56 us; 16k nodes, 8 heads, d = 16, k = 1 14.9 -> 14.3); past
-    // 256, where the LDS holds two or three waves per SIMD, 64 (d = 16, 12.5k nodes, 4
-    // heads, k = 512 263 -> 178; 51k nodes, d = 32 325 -> 266), but at wider rows that
-    // costs more registers than it gains (d = 64, 326k nodes, k = 512 2829 and 2941).
-    const int round = k <= 4 ? 4 : k > 256 && d <= 32 && dv <= 32 && parts == 1 ? 64 : 16;
+    // 64, k = 1 87 -> 56 us; 16k nodes, 8 heads, d = 16, k = 1 14.9 -> 13.3); past
+    // 256, where the LDS holds two or three waves per SIMD, 64 while a head's rows
+    // stay in the L2 (12.5k nodes, 4 heads, d = 16, k = 512 263 -> 178; 10k nodes, 4
+    // heads, d = 32, normal rows 247 -> 204).  Beyond, more rows in flight push each
+    // other out of it (30k nodes, d = 32, k = 300, normal rows 413 -> 445; 100k, d =
+    // 16, k = 512 3796 -> 4237), and wider rows cost more registers than they gain.
+    const bool in_l2 = (int64_t)N * (d + dv) <= 5 << 18;   // 2.5 of the 4 MB
+    const int round = k <= 4 ? 4 : k > 256 && d <= 32 && dv <= 32 && in_l2 && parts == 1 ? 64 : 16;
     const int32_t per_head = (N + teams - 1) / teams, head_blocks = perm == nullptr && gather_by_head(N, H, d, dv, k, one_graph) ? per_head : 0;
     const dim3 blocks = perm != nullptr   ? dim3((unsigned)per_head, (unsigned)H)
                         : head_blocks > 0 ? dim3((unsigned)((int64_t)per_head * H))

@@ -78,7 +78,7 @@ def test_given_sets(case):
 
 @pytest.mark.parametrize("N,d,dv,k", [
     (14, 16, 16, 4), (12, 64, 128, 3), (16, 16, 32, 5), (24, 128, 16, 9), (40, 32, 64, 17),
-    # up to 6144 query-heads (12288 past k = 128), four teams share one where k > 32; 64 slots a round past k = 256
+    # up to 6144 query-heads (12288 past k = 128), four teams share one where k > 32; 64 slots a round past k = 256 up to N (d + d_V) = 5 2^18
     (70, 64, 32, 33), (134, 32, 32, 64), (86, 128, 128, 40), (520, 16, 16, 257), (806, 64, 64, 400), (3072, 16, 64, 100),
     (3073, 16, 64, 100), (3100, 32, 32, 64), (6144, 32, 64, 129), (6145, 32, 64, 129), (6150, 16, 32, 300), (6150, 32, 16, 512),
     (6150, 64, 16, 257)])
