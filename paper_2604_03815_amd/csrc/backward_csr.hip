@@ -995,9 +995,9 @@ __global__ __launch_bounds__(256) void bkt_split2_kernel(const PairRecord* __res
 // 262k nodes, d = 64, k = 128 1577 -> 1124; 500k nodes, d = 16 1029 -> 988.
 // The atomics of several pieces go to neighbouring addresses from neighbouring
 // lanes (eight addresses 32 bytes apart before; us): 84k nodes, 16 heads, d = 32,
-// k = 20, normal rows (two pieces a bucket) 2025 -> 756, plain stores in their
-// place 683; 760k nodes, d = 32, k = 50 1255 -> 791; 200k nodes, 2 heads, d = 32,
-// k = 64 493 -> 465; 30k nodes, 4 heads, d = 32, k = 256 606 -> 515.
+// k = 20, normal rows (two pieces a bucket) 2025 -> 676; 760k nodes, d = 32, k =
+// 50 1255 -> 791; 200k nodes, 2 heads, d = 32, k = 64 493 -> 460; 30k nodes, 4
+// heads, d = 32, k = 256 606 -> 466.
 // (Sums in LDS with float atomics instead of the sort were six times slower:
 // an LDS float add took about four clocks a lane.)
 constexpr int kSumThreads = 512;
@@ -1018,8 +1018,14 @@ __device__ __forceinline__ void exchange_bit(float (&a)[8], int lane) {
 
 constexpr int pow2_at_least(int x) { return x <= 1 ? 1 : 2 * pow2_at_least((x + 1) / 2); }
 
+// Waves per SIMD: six, three workgroups a CU, as the LDS allows, at the widths
+// where 80 registers hold the exchange (16 clouds of 1k-4k nodes, 4 heads, d = 32,
+// k = 32 100 -> 84 us; at other unequal widths that spills ten: d = 64, d_V = 128,
+// k = 32, whole backward 571 -> 604).
+constexpr int sum_waves(int d, int dv) { return d == dv || d + dv <= 64 ? 6 : 1; }
+
 template <int D, int DV>
-__global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t* __restrict__ QG,
+__global__ __launch_bounds__(kSumThreads, sum_waves(D, DV)) void bkt_reduce_kernel(const uint16_t* __restrict__ QG,
                                                                  const BucketRecord* __restrict__ rec,
                                                                  const int32_t* __restrict__ sstart,
                                                                  const int32_t* __restrict__ pstart, int32_t nbk,
@@ -1119,11 +1125,17 @@ __global__ __launch_bounds__(kSumThreads) void bkt_reduce_kernel(const uint16_t*
                 if constexpr (T == 8) exchange_bit<4>(acc, c);
                 exchange_bit<2>(acc, c);
                 exchange_bit<1>(acc, c);
+                // (sum e is lane c0 + e's; q's lanes are the first D/8, all of an
+                // eight's or, at D < 64, the first D/8 of the first eight)
+                const int c0 = c & ~(T - 1), l = c & (T - 1);
+                float* const pk = dK + (((size_t)lo << shift) + cur) * D + 8 * c0 + l;
+                float* const pv = dV + (((size_t)lo << shift) + cur) * DV + 8 * c0 + l - D;
+                float* const first = c0 < D / 8 ? pk : pv;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const int el = 8 * ((c & ~(T - 1)) + (e & (T - 1))) + (e & ~(T - 1)) + (c & (T - 1));
-                    const size_t row = ((size_t)lo << shift) + cur;
-                    if (el < RW) atomicAdd(el < D ? dK + row * D + el : dV + row * DV + (el - D), acc[e]);
+                    const int off = 8 * (e & (T - 1)) + (e & ~(T - 1));
+                    float* const to = (e & (T - 1)) < D / 8 ? first : pv;
+                    if (c0 + (e & (T - 1)) < RW / 8) atomicAdd(to + off, acc[e]);
                 }
             }
 #pragma unroll
