@@ -103,14 +103,20 @@ constexpr size_t dense_lds_bytes() {
     return dense_list_bytes<W, T, GT, CAP, QN>() + QN * (8 + 4 + 4) + (CAP > 128 ? QN * kValueBuckets * 4 : 0);
 }
 
+// Waves per SIMD: with lists of 256 keys the LDS holds two blocks a CU, so four
+// waves, as many as the registers are held to, at 2 to 16 spilled ones (the
+// resident form at d = 128 would spill 41 and keeps three).  With lists of 128 at
+// d = 64 six, three blocks a CU, which 84 registers would make two (12 clouds of
+// 1.5k-3k nodes, 2 heads, k = 32 90 -> 79 us).
+constexpr int dense_waves(int d, int cap, int qn, int r) {
+    return cap == 256 && (d < 128 || r == 0) ? 4 : d == 64 && cap == 128 && qn == 32 && r == 0 ? 6 : 1;
+}
+
 // R > 0: resident (graphs of at most 32 W R keys, read from K itself);
 // R == 0: two passes over the tiled keys kp.  tasks == nullptr: one graph of
 // N nodes, task b being its b-th run of 32 queries (64 for QN = 64).
-// (With lists of 256 keys the LDS holds two blocks a CU: four waves per SIMD, as
-// many as the registers are held to, at 2 to 16 spilled ones; the resident form
-// at d = 128 would spill 41 and keeps three waves.)
 template <int D, int W, int T, int GT, int CAP, int QN, int R>
-__global__ __launch_bounds__(64 * W, CAP == 256 && (D < 128 || R == 0) ? 4 : 1) void dense_select_kernel(
+__global__ __launch_bounds__(64 * W, dense_waves(D, CAP, QN, R)) void dense_select_kernel(
     const uint4* __restrict__ kp, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
     const Task* __restrict__ tasks, int32_t ntasks, int32_t N, int32_t H, int32_t k, int32_t ntiles, int32_t first,
     int32_t* __restrict__ topk_idx) {
