@@ -257,7 +257,9 @@ __global__ __launch_bounds__(256) void csr_coef_kernel(
     // the rest).  With 32 (us): 760k nodes, d = 32, k = 50, normal rows 1769 ->
     // 1215 (a lane per row 1391 in the fused pass); 200k nodes, 2 heads, d = 32, k =
     // 64, city 446 -> 392; 100k nodes, 4 heads, d = 64, k = 32, normal rows 674 -> 481.
-    constexpr int kKeepRegs = NS <= 4 ? 64 : 32;
+    // Not at unequal widths (40 graphs of 100-1000 nodes, 3 heads, d = 32, d_V = 128,
+    // k = 64, whole backward 410 -> 443).
+    constexpr int kKeepRegs = NS <= 4 && D == DV ? 64 : 32;
     coef_team<D, DV, NS, kKeepRegs>(in, K, V, keep, keep_scale, H, k, scale, tl,
                          reinterpret_cast<char*>(lds) + team * coef_area(NS), dQ, nullptr, 0, jj, ca, cp);
 #pragma unroll
